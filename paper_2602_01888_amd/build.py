@@ -60,7 +60,7 @@ def stale() -> bool:
     if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
-    deps = sources() + [os.path.join(CSRC, "tomg_internal.h"),
+    deps = sources() + [os.path.join(CSRC, "tomg_internal.h"), os.path.join(CSRC, "quad.h"),
                         os.path.join(ROOT, "include", "tomg.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 

@@ -296,12 +296,8 @@ static hipError_t init_problem(tomg_problem *p, const tomg_config *cfg, const La
   }
   p->dargs = (ArgsBlob *)(w + lay.args);
   p->bout = D(lay.bout);
-  // the single-workgroup tail assumes Dirichlet rings and halves both axes;
-  // problems with a stored level-0 stencil (Neumann edges, flux form) or
-  // semi-coarsened levels run the level passes down to the coarsest solve
-  const bool no_tail = stored_level0(*cfg) || cfg->semi_levels > 0;
-  p->lc = no_tail ? p->L - 1 : tail_level(p, false);
-  p->lcb = no_tail ? p->L - 1 : tail_level(p, true);
+  p->lc = tail_level(p, false);
+  p->lcb = tail_level(p, true);
   build_pass_args(p);
   build_tail_args(p);
   build_red_args(p);

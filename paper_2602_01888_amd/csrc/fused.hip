@@ -32,6 +32,7 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "quad.h"
 #include "tomg_internal.h"
 
 namespace tomg {
@@ -119,31 +120,25 @@ struct Rec<T, false> {
 
 __device__ __forceinline__ int ring_slot(int o, int n) { return ((o % n) + n) % n; }
 
-// Off-centre sum and diagonal of the node at LDS column t+1 of rows
-// (lo, mid, hi) = (r-1, r, r+1): (A x)_c = off + dg x_c.
+// f minus the off-centre part of the operator, and the diagonal, at the node
+// at LDS column t+1 of rows (lo, mid, hi) = (r-1, r, r+1).
 template <typename T>
-__device__ __forceinline__ void apply_eps(const Rec<T, true> &c, const T *lo, const T *mid,
-                                          const T *hi, int t, T &off, T &dg) {
-  const T k1 = c.ax + c.gx, k3 = c.ax - c.gx, k4 = c.ay + c.gy, k5 = c.ay - c.gy;
-  off = k1 * mid[t + 2] + k3 * mid[t] + k4 * hi[t + 1] + k5 * lo[t + 1] +
-        c.k6 * ((hi[t + 2] - hi[t]) - (lo[t + 2] - lo[t]));
-  dg = -T(2) * (c.ax + c.ay);
+__device__ __forceinline__ T defect(const Rec<T, true> &c, const T *lo, const T *mid, const T *hi,
+                                    int t) {
+  return defect18(c.f, plain_add(c.ax, c.gx), plain_add(c.ax, -c.gx), plain_add(c.ay, c.gy),
+                  plain_add(c.ay, -c.gy), c.k6, lo[t], lo[t + 1], lo[t + 2], mid[t], mid[t + 2],
+                  hi[t], hi[t + 1], hi[t + 2]);
 }
 template <typename T>
-__device__ __forceinline__ void apply_st(const Rec<T, false> &c, const T *lo, const T *mid,
-                                         const T *hi, int t, T &off, T &dg) {
-  off = c.a[0] * lo[t] + c.a[1] * lo[t + 1] + c.a[2] * lo[t + 2] + c.a[3] * mid[t] +
-        c.a[5] * mid[t + 2] + c.a[6] * hi[t] + c.a[7] * hi[t + 1] + c.a[8] * hi[t + 2];
-  dg = c.a[4];
+__device__ __forceinline__ T defect(const Rec<T, false> &c, const T *lo, const T *mid,
+                                    const T *hi, int t) {
+  return defect9(c.f, c.a, lo[t], lo[t + 1], lo[t + 2], mid[t], mid[t + 2], hi[t], hi[t + 1],
+                 hi[t + 2]);
 }
-template <typename T, bool EPS>
-__device__ __forceinline__ void apply(const Rec<T, EPS> &c, const T *lo, const T *mid, const T *hi,
-                                      int t, T &off, T &dg) {
-  if constexpr (EPS)
-    apply_eps<T>(c, lo, mid, hi, t, off, dg);
-  else
-    apply_st<T>(c, lo, mid, hi, t, off, dg);
-}
+template <typename T>
+__device__ __forceinline__ T diag(const Rec<T, true> &c) { return eps_diag(c.ax, c.ay); }
+template <typename T>
+__device__ __forceinline__ T diag(const Rec<T, false> &c) { return c.a[4]; }
 
 template <typename T, int BW>
 __device__ __forceinline__ T block_sum(T v, T *red) {
@@ -375,11 +370,12 @@ __device__ __forceinline__ void pass_body(const PassArgs<T> &a, const int bx, co
             // raw row v + 2 is the grid row above v + 1 (below it when MIR)
             const T dxy = MIR ? rxy[v] - rxy[v + 2] : rxy[v + 2] - rxy[v];
             const T dyy = MIR ? ryy[v] - ryy[v + 2] : ryy[v + 2] - ryy[v];
-            R.gx = (xch[2 * v][t + 2] - xch[2 * v][t]) * a.qx + dxy * a.qxy;
-            R.gy = dyy * a.qy + (xch[2 * v + 1][t + 2] - xch[2 * v + 1][t]) * a.qxy;
+            eps_coefs(xch[2 * v][t + 2] - xch[2 * v][t], dyy,
+                      xch[2 * v + 1][t + 2] - xch[2 * v + 1][t], dxy, a.qx, a.qy, a.qxy, R.gx,
+                      R.gy);
             R.k6 = rxy[v + 1] * a.hxy;
             R.f = rff[v + 1];
-            R.ik = rdd[v + 1] ? T(0) : T(-1) / (T(2) * (R.ax + R.ay));
+            R.ik = rdd[v + 1] ? T(0) : T(1) / eps_diag(R.ax, R.ay);
           }
         } else {
 #pragma unroll
@@ -407,9 +403,7 @@ __device__ __forceinline__ void pass_body(const PassArgs<T> &a, const int bx, co
                 const Rec<T, EPS> &R = rec[slot(rel0 + o)];
                 if (rowok && updc && odd == cp && R.ik != T(0)) {
                   T *mid = lrow(r);
-                  T off, dg;
-                  apply<T, EPS>(R, below_row(r), mid, above_row(r), t, off, dg);
-                  mid[t + 1] = (R.f - off) * R.ik;
+                  mid[t + 1] = relaxed(defect(R, below_row(r), mid, above_row(r), t), R.ik);
                 }
               }
               __syncthreads();
@@ -427,9 +421,8 @@ __device__ __forceinline__ void pass_body(const PassArgs<T> &a, const int bx, co
           if (RESTRICT || NORM) {
             const bool rowok = relaxable(r);
             if (rowok && updc && R.ik != T(0)) {
-              T off, dg;
-              apply<T, EPS>(R, below_row(r), mid, above_row(r), t, off, dg);
-              res[q] = R.f - off - dg * mid[t + 1];
+              res[q] = residual_of(defect(R, below_row(r), mid, above_row(r), t), diag(R),
+                                   mid[t + 1]);
             }
           }
           if (r >= y0 && r < y1 && outc) {

@@ -2143,14 +2143,13 @@ static int coarse_solve_threads(const tomg_problem *p) {
 }
 
 // First level handed to the single-workgroup tail: the first coarse level
-// with at most tail_max_nodes() nodes and at most 4 levels below it.
+// from which it fits (tail_fits).
 int tail_level(const tomg_problem *p, bool batch) {
-  // the tail gives each thread one node of its two coarsest levels: a large
-  // coarsest level is solved on its own below the fused passes
+  // a large coarsest level is solved on its own below the fused passes
   if (p->cband || (long)p->lv[p->L - 1].nx * p->lv[p->L - 1].ny > kSmallCoarseNodes)
     return p->L - 1;
   for (int l = 1; l < p->L; ++l)
-    if ((long)p->lv[l].nx * p->lv[l].ny <= tail_max_nodes(batch) && p->L - l <= 4) return l;
+    if (tail_fits(p, l, batch)) return l;
   return p->L - 1;
 }
 namespace {
@@ -2208,19 +2207,11 @@ static void coarse_levels(tomg_problem *p, const EpsOp<T> &op0, const LevelView<
   for (int l = 1; l < lc; ++l)
     fused_down<T>(p, l, views[l].x, views[l].pong, views[l].b, op0.exx, op0.exy, op0.eyy,
                   views[l].st, views[l + 1].b, true);
-  T *xs[kMaxLevels];
-  T *bs[kMaxLevels];
-  const T *sts[kMaxLevels];
-  for (int l = 0; l < L; ++l) {
-    xs[l] = views[l].x;
-    bs[l] = views[l].b;
-    sts[l] = views[l].st;
-  }
   if (lc == L - 1)  // no tail: the coarsest solve alone
     hipLaunchKernelGGL((k_coarse_solve<T>), 1, coarse_solve_threads(p), 0, p->stream, p->cinv,
                        p->cidx, (const T *)views[L - 1].b, views[L - 1].x, (int)p->lv[L - 1].n);
   else
-    tail_cycle<T>(p, lc, xs, bs, sts);
+    tail_cycle<T>(p);
   for (int l = lc - 1; l >= 1; --l)
     fused_up<T>(p, l, views[l].pong, views[l].x, views[l].b, op0.exx, op0.exy, op0.eyy,
                 views[l].st, views[l + 1].x, nullptr);

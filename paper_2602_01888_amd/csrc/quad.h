@@ -1,0 +1,174 @@
+// A 2 x 2 quad of grid nodes held by one thread: the four nodes of a quad
+// have the four colours of the four-colour Gauss-Seidel sweep, so in every
+// colour phase each thread relaxes exactly one node of its own and no lane
+// idles.  The quad's stencils, right-hand side and iterate stay in registers;
+// the iterate is mirrored in LDS, one plane per quad position, so that a
+// phase reads the five neighbours outside the quad with unit stride across
+// lanes.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+namespace tomg {
+
+// ---- arithmetic of one node ---------------------------------------------
+// Every kernel that relaxes nodes (level passes, tiles, tail) forms a node's
+// value from these functions alone.  Each multiply-add is written out and
+// contraction is off: left to the compiler, which product of a sum becomes
+// the fused one depends on where its operands live, and a problem solved
+// alone and in a batch, by different kernels, must agree bit for bit.
+
+// f minus the off-centre part of a stored 9-point stencil (two chains of
+// four multiply-adds: half the latency of one of eight).
+template <typename T>
+__device__ __forceinline__ T defect9(T f, const T *a, T sw, T s, T se, T w, T e, T nw, T n,
+                                     T ne) {
+#pragma clang fp contract(off)
+  T p = __builtin_elementwise_fma(-a[0], sw, f), q = a[5] * e;
+  p = __builtin_elementwise_fma(-a[1], s, p);
+  q = __builtin_elementwise_fma(a[6], nw, q);
+  p = __builtin_elementwise_fma(-a[2], se, p);
+  q = __builtin_elementwise_fma(a[7], n, q);
+  p = __builtin_elementwise_fma(-a[3], w, p);
+  q = __builtin_elementwise_fma(a[8], ne, q);
+  return p - q;
+}
+// The same for eq. 18: k1, k3, k4, k5 the E, W, N, S neighbours, k6 the
+// diagonal difference.
+template <typename T>
+__device__ __forceinline__ T defect18(T f, T k1, T k3, T k4, T k5, T k6, T sw, T s, T se, T w,
+                                      T e, T nw, T n, T ne) {
+#pragma clang fp contract(off)
+  const T x = (ne - nw) - (se - sw);
+  T p = __builtin_elementwise_fma(-k1, e, f), q = k4 * n;
+  p = __builtin_elementwise_fma(-k3, w, p);
+  q = __builtin_elementwise_fma(k5, s, q);
+  q = __builtin_elementwise_fma(k6, x, q);
+  return p - q;
+}
+template <typename T>
+__device__ __forceinline__ T relaxed(T defect, T ik) { return defect * ik; }
+template <typename T>
+__device__ __forceinline__ T residual_of(T defect, T dg, T x) {
+  return __builtin_elementwise_fma(-dg, x, defect);
+}
+// Coefficients of eq. 18 at a node from the tensor there and the differences
+// of its components across the node (dxx = eps_xx E - W, dyy = eps_yy N - S,
+// xyx and xyy those of eps_xy); k1 = ax + gx, k3 = ax - gx, k4 = ay + gy,
+// k5 = ay - gy, diagonal -2 (ax + ay).
+template <typename T>
+__device__ __forceinline__ void eps_coefs(T dxx, T dyy, T xyx, T xyy, T qx, T qy, T qxy, T &gx,
+                                          T &gy) {
+#pragma clang fp contract(off)
+  gx = __builtin_elementwise_fma(dxx, qx, xyy * qxy);
+  gy = __builtin_elementwise_fma(dyy, qy, xyx * qxy);
+}
+template <typename T>
+__device__ __forceinline__ T plain_add(T a, T b) {
+#pragma clang fp contract(off)
+  return a + b;
+}
+template <typename T>
+__device__ __forceinline__ T eps_diag(T ax, T ay) { return T(-2) * plain_add(ax, ay); }
+
+// ---- quads -----------------------------------------------------------------
+
+// Position k = a + 2 b of a node in its quad (a along x, b along y).
+template <typename T>
+struct Quad {
+  T f[4], ik[4], x[4];  // ik: 1 / diagonal, 0 where the node is not relaxed
+};
+// Stored 9-point stencil (plane order of the level), and eq. 18's
+// coefficients with the diagonal.
+template <typename T>
+struct QuadSt : Quad<T> {
+  T a[4][9];
+};
+template <typename T>
+struct QuadEps : Quad<T> {
+  T k1[4], k3[4], k4[4], k5[4], k6[4], dg[4];
+};
+
+// Neighbour (di, dj) of position k: from the thread's own quad, or from the
+// LDS plane of the neighbour's position.  c points at the thread's entry of
+// plane 0; ps and pitch are the plane size and its row pitch.
+template <typename T>
+__device__ __forceinline__ T quad_nb(const T (&x)[4], const T *c, int k, int di, int dj, int ps,
+                                     int pitch) {
+  const int a = (k & 1) + di, b = (k >> 1) + dj;
+  const int pos = (a & 1) + 2 * (b & 1);
+  if (a >= 0 && a < 2 && b >= 0 && b < 2) return x[pos];
+  const int du = a < 0 ? -1 : (a > 1 ? 1 : 0), dv = b < 0 ? -1 : (b > 1 ? 1 : 0);
+  return c[pos * ps + dv * pitch + du];
+}
+
+// f minus the off-centre part of the operator at position k.
+template <typename T, typename Q>
+__device__ __forceinline__ T quad_defect(const Q &q, const T *c, int k, int ps, int pitch) {
+  const T sw = quad_nb(q.x, c, k, -1, -1, ps, pitch), s = quad_nb(q.x, c, k, 0, -1, ps, pitch);
+  const T se = quad_nb(q.x, c, k, 1, -1, ps, pitch), w = quad_nb(q.x, c, k, -1, 0, ps, pitch);
+  const T e = quad_nb(q.x, c, k, 1, 0, ps, pitch), nw = quad_nb(q.x, c, k, -1, 1, ps, pitch);
+  const T n = quad_nb(q.x, c, k, 0, 1, ps, pitch), ne = quad_nb(q.x, c, k, 1, 1, ps, pitch);
+  if constexpr (std::is_same<Q, QuadSt<T>>::value)
+    return defect9(q.f[k], q.a[k], sw, s, se, w, e, nw, n, ne);
+  else
+    return defect18(q.f[k], q.k1[k], q.k3[k], q.k4[k], q.k5[k], q.k6[k], sw, s, se, w, e, nw, n,
+                    ne);
+}
+template <typename T>
+__device__ __forceinline__ T quad_diag(const QuadSt<T> &q, int k) { return q.a[k][4]; }
+template <typename T>
+__device__ __forceinline__ T quad_diag(const QuadEps<T> &q, int k) { return q.dg[k]; }
+
+// One colour phase: the node at position k, in registers and in LDS.
+template <typename T, typename Q>
+__device__ __forceinline__ void quad_relax(Q &q, T *c, int k, int ps, int pitch) {
+  if (q.ik[k] != T(0)) {
+    q.x[k] = relaxed(quad_defect<T>(q, c, k, ps, pitch), q.ik[k]);
+    c[k * ps] = q.x[k];
+  }
+}
+
+// Residual at position k, 0 where the node is not relaxed.
+template <typename T, typename Q>
+__device__ __forceinline__ T quad_resid(const Q &q, const T *c, int k, int ps, int pitch) {
+  if (q.ik[k] == T(0)) return T(0);
+  return residual_of(quad_defect<T>(q, c, k, ps, pitch), quad_diag(q, k), q.x[k]);
+}
+
+// Full weighting of the residuals around position kc of the thread's quad
+// (res: its own; cr: its entry of the residual planes).
+template <typename T>
+__device__ __forceinline__ T quad_full_weight(const T (&res)[4], const T *cr, int kc, int ps,
+                                              int pitch) {
+  T col[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const T lo = quad_nb(res, cr, kc, d - 1, -1, ps, pitch);
+    const T mid = quad_nb(res, cr, kc, d - 1, 0, ps, pitch);
+    const T hi = quad_nb(res, cr, kc, d - 1, 1, ps, pitch);
+    col[d] = lo + T(2) * mid + hi;
+  }
+  return (col[0] + T(2) * col[1] + col[2]) * T(0.0625);
+}
+
+// Two neighbouring elements of a row in one load (rows have no alignment
+// beyond that of an element).
+template <typename T>
+struct PairOf;
+template <>
+struct PairOf<double> {
+  typedef double type __attribute__((ext_vector_type(2), aligned(8)));
+};
+template <>
+struct PairOf<float> {
+  typedef float type __attribute__((ext_vector_type(2), aligned(4)));
+};
+template <typename T>
+__device__ __forceinline__ typename PairOf<T>::type load_pair(const T *p) {
+  return *reinterpret_cast<const typename PairOf<T>::type *>(p);
+}
+
+}  // namespace tomg

@@ -2,361 +2,468 @@
 // Section 3).
 //
 // Below a few thousand nodes per level, a level pass is bound by latency: a
-// launch per pass, or a band-marching pass with a barrier per colour phase
-// and row pair, costs far more than its work.  One 1024-thread workgroup
-// runs the sub-cycle from level lc (zero start, right-hand side from the
-// level above) down to the coarsest level and back, with the iterates of
-// all tail levels and one residual array in LDS, so a colour phase is an
-// LDS read-modify-write between two barriers.
+// launch per pass costs more than its work.  One workgroup runs the
+// sub-cycle from level lc (zero start, right-hand side from the level above)
+// down to the coarsest level and back.
 //
-// Levels are counted from the coarsest (r = 0).  The two coarsest (at most
-// 17 x 17 nodes) give each thread one node whose stencil row and right-hand
-// side stay in registers.  Levels r >= 2 (at most 65 x 65 nodes, five nodes
-// per thread) stream their stencil rows from global memory, where they stay
-// in the L2 cache; in each colour phase a thread already loads the stencil
-// of its node of the next phase, so the load latency overlaps the barrier.
-// Their right-hand side is the global array for the first tail level and an
-// LDS array below it.  Arithmetic per node is that of the other kernels:
-// four-colour Gauss-Seidel on the stored 9-point stencil, full weighting,
-// bilinear prolongation, explicit coarsest inverse.
+// Levels are counted from the coarsest (r = 0).  On every level above the
+// coarsest a thread owns at most one 2 x 2 quad of nodes (quad.h): stencils,
+// right-hand side and iterate in registers, the iterate mirrored in LDS
+// planes, so a colour phase is five LDS reads, nine multiply-adds and one
+// LDS write between two barriers, with every lane of an owning wave busy,
+// and each stencil is read from memory once per level and cycle.  (With one
+// node per thread and the stencil row streamed from L2 in every phase, half
+// of the 34 us of a cycle from 33 x 33 was that streaming.)  A level of at
+// most 64 quads belongs to one wave, whose phases need no barrier.  Levels
+// below the first have their owners in other waves where there are enough
+// of them, and keep their stencils too; the 1024-thread form has no
+// registers for that and loads the stencils of its lower levels, and the
+// first level's again on the way up, when they are needed.
+//
+// FREE: the outer ring may hold unknowns (Neumann edges; any stored level-0
+// stencil).  Then quads start at node 0; otherwise at node 1, so that the
+// 63 x 63 inner nodes of a 65 x 65 level are exactly 1024 quads.
+// Arithmetic per node is that of the other kernels: four-colour Gauss-Seidel
+// on the stored 9-point stencil, full weighting, bilinear prolongation,
+// explicit coarsest inverse (staged in LDS).
 #include <type_traits>
 
+#include "quad.h"
 #include "tomg_internal.h"
 
 namespace tomg {
 namespace {
 
-constexpr int kTailThreads = 1024;
-constexpr int kTailMaxNodes = 65 * 65;  // per level: at most five nodes per thread
-// LDS per workgroup, less the static arrays (the coarsest right-hand side)
-constexpr int kTailLdsMax = 160 * 1024 - 9 * 1024;
+constexpr int kTailWide = 1024, kTailNarrow = 512;  // threads of the two forms
+constexpr int kTailMaxNodes = 65 * 65;              // per level
+constexpr int kTailLdsMax = 160 * 1024 - 2 * 1024;
+static_assert(kMaxCoarseNodes <= kMaxCoarseUnknowns * kMaxCoarseUnknowns,
+              "the coarsest solve alone keeps its right-hand side where the inverse is staged");
 
-template <typename T>
-struct Own {
-  T a[9];
-  T b, ik;  // ik = 1 / diagonal, 0 where the node is not relaxed
-  int c;    // node index in the level, -1 when not owned
-  int col;  // colour (i mod 2) + 2 (j mod 2)
-};
-
-// Interior node k of colour col (i = pi + 2u, j = pj + 2w), or -1.
-__device__ __forceinline__ int colour_node(int nx, int ny, int col, int k) {
-  const int i0 = (col & 1) ? 1 : 2, j0 = (col >> 1) ? 1 : 2;
-  const int cu = nx - 2 >= i0 ? (nx - 2 - i0) / 2 + 1 : 0;
-  const int cw = ny - 2 >= j0 ? (ny - 2 - j0) / 2 + 1 : 0;
-  if (k >= cu * cw) return -1;
-  return (j0 + 2 * (k / cu)) * nx + i0 + 2 * (k % cu);
-}
-
-template <typename T>
+template <typename T, int NT, bool FREE>
 __device__ __forceinline__ void tail_body(const TailArgs<T> &a) {
-  extern __shared__ unsigned char smem_raw[];
-  T *X = reinterpret_cast<T *>(smem_raw);
-  __shared__ double bb[kMaxCoarseNodes];
+  constexpr int OFF = FREE ? 0 : 1;
+  constexpr bool KEEP = NT < kTailWide;  // registers for a lower level's quad beside the first's
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  __shared__ double bb[kSmallCoarseNodes];
+  __shared__ int ci[kSmallCoarseNodes + 1];
+  double *cinv = reinterpret_cast<double *>(smem_raw);
+  T *S = reinterpret_cast<T *>(cinv + kMaxCoarseUnknowns * kMaxCoarseUnknowns);
   const int t = threadIdx.x;
   const int nl = a.nl;
-  int total = 0, rmax = 0;
-  for (int q = 0; q < nl; ++q) {
-    const int n = a.lv[q].nx * a.lv[q].ny;
-    total += n;
-    if (q < nl - 1) rmax = max(rmax, n);
-  }
-  T *Rb = X + total;  // residual of the level being restricted
-  T *Bs = Rb + rmax;  // right-hand sides of streamed levels below the first
   auto lvl = [&](int r) -> const TailLevel<T> & { return a.lv[nl - 1 - r]; };
+  // position in its quad of the nodes of colour col
+  auto pos = [](int col) { return FREE ? col : 3 - col; };
 
-  for (int q = 0; q < nl; ++q) {
-    const TailLevel<T> &v = a.lv[q];
-    for (int c = t; c < v.nx * v.ny; c += kTailThreads) X[v.off + c] = T(0);
-  }
-  Own<T> own[2];  // levels r = 0 (coarsest) and r = 1
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    Own<T> &o = own[r];
-    o.c = -1;
-    o.b = o.ik = T(0);
-    o.col = 0;
-#pragma unroll
-    for (int z = 0; z < 9; ++z) o.a[z] = T(0);
-    if (r >= nl) continue;
-    const TailLevel<T> &v = lvl(r);
-    const int n = v.nx * v.ny;
-    if (t >= n) continue;
-    const int i = t % v.nx, j = t / v.nx;
-    o.c = t;
-    o.col = (i & 1) + 2 * (j & 1);
-    const bool interior = i > 0 && j > 0 && i < v.nx - 1 && j < v.ny - 1;
-    if (r > 0 && interior && !v.dir[t]) {
-#pragma unroll
-      for (int z = 0; z < 9; ++z) o.a[z] = v.st[(size_t)z * n + t];
-      o.ik = T(1) / o.a[4];
-    }
-    if (r == nl - 1) o.b = v.b[t];
-  }
-  __syncthreads();
-
-  // off-centre part of A x at node c of level v, from a stencil row s9
-  auto offc = [&](const TailLevel<T> &v, const T *s9, int c) -> T {
-    const T *x = X + v.off;
-    const int w = v.nx;
-    return s9[0] * x[c - w - 1] + s9[1] * x[c - w] + s9[2] * x[c - w + 1] + s9[3] * x[c - 1] +
-           s9[5] * x[c + 1] + s9[6] * x[c + w - 1] + s9[7] * x[c + w] + s9[8] * x[c + w + 1];
+  // the quad of level r that this thread owns (-1: none)
+  auto owned = [&](const TailLevel<T> &v) {
+    const int q = t - v.t0;
+    return q >= 0 && q < v.nq ? q : -1;
   };
-  auto load_row = [&](const TailLevel<T> &v, int c, T s9[9]) {
+  // stencils of quad q of level v; nodes that are not relaxed get ik = 0
+  auto load_quad = [&](const TailLevel<T> &v, int q, QuadSt<T> &Q) {
+    const int u = q % v.qx, w = q / v.qx;
+    const int i0 = 2 * u + OFF, j0 = 2 * w + OFF;
+    const int ib = min(i0, v.nx - 2);
+    const bool last = i0 > ib;  // the pair starts at the last column
     const size_t n = (size_t)v.nx * v.ny;
 #pragma unroll
-    for (int z = 0; z < 9; ++z) s9[z] = v.st[z * n + c];
-  };
-  auto rhs = [&](const TailLevel<T> &v, int c) -> T { return v.boff < 0 ? v.b[c] : Bs[v.boff + c]; };
-
-  auto smooth = [&](int r, int sweeps) {
-    const TailLevel<T> &v = lvl(r);
-    if (r >= 2) {
-      // the node k = t of each colour, its stencil loaded one phase ahead
-      T s9n[9];
-      int cn = colour_node(v.nx, v.ny, 0, t), dn = 1;
-      if (cn >= 0) {
-        dn = v.dir[cn];
-        load_row(v, cn, s9n);
-      }
-      for (int s = 0; s < sweeps; ++s)
-        for (int col = 0; col < 4; ++col) {
-          T s9[9];
+    for (int b = 0; b < 2; ++b) {
+      const size_t c = (size_t)min(j0 + b, v.ny - 1) * v.nx + ib;
 #pragma unroll
-          for (int z = 0; z < 9; ++z) s9[z] = s9n[z];
-          const int c = cn, d = dn;
-          if (s + 1 < sweeps || col < 3) {
-            cn = colour_node(v.nx, v.ny, (col + 1) & 3, t);
-            if (cn >= 0) {
-              dn = v.dir[cn];
-              load_row(v, cn, s9n);
-            }
-          }
-          if (c >= 0 && !d) X[v.off + c] = (rhs(v, c) - offc(v, s9, c)) * (T(1) / s9[4]);
-          for (int k = t + kTailThreads;; k += kTailThreads) {  // nodes beyond the first
-            const int c2 = colour_node(v.nx, v.ny, col, k);
-            if (c2 < 0) break;
-            if (v.dir[c2]) continue;
-            T s2[9];
-            load_row(v, c2, s2);
-            X[v.off + c2] = (rhs(v, c2) - offc(v, s2, c2)) * (T(1) / s2[4]);
-          }
+      for (int z = 0; z < 9; ++z) {
+        const auto p = load_pair(v.st + z * n + c);
+        Q.a[2 * b][z] = last ? p[1] : p[0];
+        Q.a[2 * b + 1][z] = p[1];
+      }
+      const int d0 = v.dir[last ? c + 1 : c], d1 = v.dir[c + 1];
+      const bool row = j0 + b < v.ny - OFF;
+      Q.ik[2 * b] = row && i0 < v.nx - OFF && !d0 ? T(1) / Q.a[2 * b][4] : T(0);
+      Q.ik[2 * b + 1] = row && i0 + 1 < v.nx - OFF && !d1 ? T(1) / Q.a[2 * b + 1][4] : T(0);
+    }
+  };
+  auto entry = [&](const TailLevel<T> &v, int q) {  // of quad q in a plane
+    return (q / v.qx + 1) * v.pitch + q % v.qx + 1;
+  };
+  // `sweeps` sweeps of level v by the owners of its quads; a level of one
+  // wave needs no barrier (the caller leaves out the other waves)
+  auto smooth = [&](const TailLevel<T> &v, QuadSt<T> &Q, int q, int sweeps, bool one_wave) {
+    T *c = S + v.xoff + (q >= 0 ? entry(v, q) : 0);
+    for (int s = 0; s < sweeps; ++s)
+#pragma unroll
+      for (int col = 0; col < 4; ++col) {
+        if (q >= 0) quad_relax<T>(Q, c, pos(col), v.ps, v.pitch);
+        if (one_wave) {
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+        } else {
           __syncthreads();
         }
-    } else {
-      const Own<T> &o = own[r & 1];
-      for (int s = 0; s < sweeps; ++s)
-        for (int col = 0; col < 4; ++col) {
-          if (o.c >= 0 && o.col == col && o.ik != T(0))
-            X[v.off + o.c] = (o.b - offc(v, o.a, o.c)) * o.ik;
-          __syncthreads();
-        }
+      }
+  };
+  // value of coarse node (I, J) of level r
+  auto coarse = [&](int r, const TailLevel<T> &v, int I, int J) -> T {
+    if (r == 0) return S[v.xoff + J * v.nx + I];
+    const int i = I - OFF, j = J - OFF;
+    return S[v.xoff + ((i & 1) + 2 * (j & 1)) * v.ps + ((j >> 1) + 1) * v.pitch + (i >> 1) + 1];
+  };
+  // iterate of level v to global memory (its Dirichlet ring is zero)
+  auto store = [&](const TailLevel<T> &v, const QuadSt<T> &Q, int q) {
+    const int u = q % v.qx, w = q / v.qx;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int i = 2 * u + OFF + (k & 1), j = 2 * w + OFF + (k >> 1);
+      if (i < v.nx && j < v.ny) v.x[(size_t)j * v.nx + i] = Q.x[k];
+      if (!FREE) {
+        if (u == 0 && (k & 1) == 0 && j < v.ny) v.x[(size_t)j * v.nx] = T(0);
+        if (w == 0 && k < 2 && i < v.nx) v.x[i] = T(0);
+        if (q == 0 && k == 0) v.x[0] = T(0);
+      }
     }
   };
 
+  const TailLevel<T> &top = a.lv[0], &cl = a.lv[nl - 1];
+  const int nco = cl.nx * cl.ny;
+  const int m = a.cidx[nco];
+  if (nl == 1) {  // the coarsest solve alone (a batch; up to kMaxCoarseNodes nodes)
+    for (int c = t; c < nco; c += NT)
+      if (a.cidx[c] >= 0) cinv[a.cidx[c]] = (double)cl.b[c];
+    __syncthreads();
+    for (int c = t; c < nco; c += NT) {
+      const int k = a.cidx[c];
+      double s = 0.0;
+      if (k >= 0)
+        for (int q = 0; q < m; ++q) s += a.cinv[(size_t)q * m + k] * cinv[q];
+      cl.x[c] = (T)s;
+    }
+    return;
+  }
+  // everything the launch reads from memory, issued together
+  const int qt = owned(top);
+  QuadSt<T> Q, Ql;  // the first level's quad; a lower level's
+  int ql = -1, rl = -1;
+  if (qt >= 0) {
+    load_quad(top, qt, Q);
+    const int u = qt % top.qx, w = qt / top.qx;
 #pragma unroll
-  for (int r = kTailLevels - 1; r >= 1; --r) {
-    if (r > nl - 1) continue;
+    for (int k = 0; k < 4; ++k) {
+      const int i = min(2 * u + OFF + (k & 1), top.nx - 1);
+      const int j = min(2 * w + OFF + (k >> 1), top.ny - 1);
+      Q.f[k] = top.b[(size_t)j * top.nx + i];
+      Q.x[k] = T(0);
+    }
+  }
+  for (int r = nl - 2; r >= 1; --r) {
+    const int q = owned(lvl(r));
+    if (q >= 0) {
+      ql = q;
+      rl = r;
+    }
+  }
+  if constexpr (KEEP) {
+    if (ql >= 0) load_quad(lvl(rl), ql, Ql);
+  }
+  for (int c = t; c < a.lds; c += NT) S[c] = T(0);
+  for (int c = t; c < m * m; c += NT) cinv[c] = a.cinv[c];
+  if (t < nco) ci[t] = a.cidx[t];
+  __syncthreads();
+
+  QuadSt<T> &L = KEEP ? Ql : Q;  // registers of the lower levels
+  for (int r = nl - 1; r >= 1; --r) {
     const TailLevel<T> &v = lvl(r), &cv = lvl(r - 1);
-    smooth(r, a.nu1);
-    // residual into Rb, then full weighting into the coarse right-hand side
-    if (r >= 2) {
-      const int n = v.nx * v.ny;
-      for (int c = t; c < n; c += kTailThreads) {
-        const int i = c % v.nx, j = c / v.nx;
-        T res = T(0);
-        if (i > 0 && j > 0 && i < v.nx - 1 && j < v.ny - 1 && !v.dir[c]) {
-          T s9[9];
-          load_row(v, c, s9);
-          res = rhs(v, c) - offc(v, s9, c) - s9[4] * X[v.off + c];
+    const bool first = r == nl - 1;
+    const int q = first ? qt : (rl == r ? ql : -1);
+    const bool one_wave = v.nq <= 64;
+    const int c0 = v.xoff + (q >= 0 ? entry(v, q) : 0);
+    const int r0 = v.roff + (q >= 0 ? entry(v, q) : 0);
+    T res[4] = {T(0), T(0), T(0), T(0)};
+    // sweeps, then the residual into the residual planes
+    auto work = [&](QuadSt<T> &P) {
+      smooth(v, P, q, a.nu1, one_wave);
+      if (q >= 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          res[k] = quad_resid<T>(P, S + c0, k, v.ps, v.pitch);
+          S[r0 + k * v.ps] = res[k];
         }
-        Rb[c] = res;
       }
+    };
+    if (first) {
+      if (!one_wave || t < 64) work(Q);
     } else {
-      const Own<T> &o = own[r & 1];
-      if (o.c >= 0)
-        Rb[o.c] = o.ik != T(0) ? o.b - offc(v, o.a, o.c) - o.a[4] * X[v.off + o.c] : T(0);
+      if (q >= 0) {
+        if constexpr (!KEEP) load_quad(v, q, L);
+        const int u = q % v.qx, w = q / v.qx;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int i = min(2 * u + OFF + (k & 1), v.nx - 1);
+          const int j = min(2 * w + OFF + (k >> 1), v.ny - 1);
+          L.f[k] = S[v.foff + j * v.nx + i];
+          L.x[k] = T(0);
+        }
+      }
+      if (!one_wave || (t >> 6) == (v.t0 >> 6)) work(L);
     }
     __syncthreads();
-    const int nc = cv.nx * cv.ny;
-    for (int C = t; C < nc; C += kTailThreads) {
-      const int I = C % cv.nx, J = C / cv.nx;
-      T s = T(0);
-      if (I > 0 && J > 0 && I < cv.nx - 1 && J < cv.ny - 1) {
-        const int f = (2 * J) * v.nx + 2 * I, w = v.nx;
-        const T e = Rb[f - w] + T(2) * Rb[f] + Rb[f + w];
-        const T ww = Rb[f - w - 1] + T(2) * Rb[f - 1] + Rb[f + w - 1];
-        const T ee = Rb[f - w + 1] + T(2) * Rb[f + 1] + Rb[f + w + 1];
-        s = (ww + T(2) * e + ee) * T(0.0625);
+    if (q >= 0) {
+      const int I = q % v.qx + OFF, J = q / v.qx + OFF;
+      if (I < cv.nx - OFF && J < cv.ny - OFF) {
+        T s = quad_full_weight(res, S + r0, FREE ? 0 : 3, v.ps, v.pitch);
+        if (FREE) {
+          const bool ring = I == 0 || J == 0 || I == cv.nx - 1 || J == cv.ny - 1;
+          // a coarse ring node is Dirichlet unless its edge is Neumann
+          if (ring && cv.dir[J * cv.nx + I]) s = T(0);
+        }
+        S[cv.foff + J * cv.nx + I] = s;
       }
-      if (r - 1 >= 2)
-        Bs[cv.boff + C] = s;
-      else
-        own[(r - 1) & 1].b = s;  // C == t: the level has at most 289 nodes
     }
     __syncthreads();
   }
   {  // coarsest level: x = A^-1 b
-    const TailLevel<T> &v = lvl(0);
-    const int n = v.nx * v.ny, m = a.cidx[n];
-    if (t < n) {
-      const int k = a.cidx[t];
-      if (k >= 0) bb[k] = (double)own[0].b;
-    }
+    if (t < nco && ci[t] >= 0) bb[ci[t]] = (double)S[cl.foff + t];
     __syncthreads();
-    if (t < n) {
-      const int k = a.cidx[t];
+    if (t < nco) {
+      const int k = ci[t];
       double s = 0.0;
       if (k >= 0)
-        for (int q = 0; q < m; ++q) s += a.cinv[(size_t)q * m + k] * bb[q];
-      X[v.off + t] = (T)s;
+        for (int q = 0; q < m; ++q) s += cinv[q * m + k] * bb[q];
+      S[cl.xoff + t] = (T)s;
+      cl.x[t] = (T)s;
     }
     __syncthreads();
   }
-#pragma unroll
-  for (int r = 1; r < kTailLevels; ++r) {
-    if (r > nl - 1) continue;
+  for (int r = 1; r < nl; ++r) {
     const TailLevel<T> &v = lvl(r), &cv = lvl(r - 1);
-    const T *xc = X + cv.off;
-    const int n = v.nx * v.ny;
-    for (int c = t; c < n; c += kTailThreads) {
-      const int i = c % v.nx, j = c / v.nx;
-      if (i == 0 || j == 0 || i == v.nx - 1 || j == v.ny - 1 || v.dir[c]) continue;
-      const int I = i >> 1, J = j >> 1;
-      const T *r0 = xc + J * cv.nx;
-      T e0 = (i & 1) ? T(0.5) * (r0[I] + r0[I + 1]) : r0[I];
-      if (j & 1) {
-        const T *r1 = r0 + cv.nx;
-        const T e1 = (i & 1) ? T(0.5) * (r1[I] + r1[I + 1]) : r1[I];
-        e0 = T(0.5) * (e0 + e1);
+    const bool first = r == nl - 1;
+    const int q = first ? qt : (rl == r ? ql : -1);
+    const bool one_wave = v.nq <= 64;
+    auto work = [&](QuadSt<T> &P) {
+      if (q >= 0) {
+        const int u = q % v.qx, w = q / v.qx;
+        T *c = S + v.xoff + entry(v, q);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if (!KEEP && first && rl >= 0) P.x[k] = c[k * v.ps];  // registers re-used below
+          if (P.ik[k] != T(0)) {
+            const int i = 2 * u + OFF + (k & 1), j = 2 * w + OFF + (k >> 1);
+            const int I = i >> 1, J = j >> 1;
+            T e = coarse(r - 1, cv, I, J);
+            if (i & 1) e = T(0.5) * (e + coarse(r - 1, cv, I + 1, J));
+            if (j & 1) {
+              T e1 = coarse(r - 1, cv, I, J + 1);
+              if (i & 1) e1 = T(0.5) * (e1 + coarse(r - 1, cv, I + 1, J + 1));
+              e = T(0.5) * (e + e1);
+            }
+            P.x[k] += e;
+            c[k * v.ps] = P.x[k];
+          }
+        }
       }
-      X[v.off + c] += e0;
+      if (one_wave) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      } else {
+        __syncthreads();
+      }
+      smooth(v, P, q, a.nu2, one_wave);
+      if (q >= 0) store(v, P, q);
+    };
+    if (first) {
+      if constexpr (!KEEP) {
+        if (qt >= 0 && rl >= 0) {
+          load_quad(top, qt, Q);
+          const int u = qt % top.qx, w = qt / top.qx;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const int i = min(2 * u + OFF + (k & 1), top.nx - 1);
+            const int j = min(2 * w + OFF + (k >> 1), top.ny - 1);
+            Q.f[k] = top.b[(size_t)j * top.nx + i];
+          }
+        }
+      }
+      if (!one_wave || t < 64) work(Q);
+    } else if (!one_wave || (t >> 6) == (v.t0 >> 6)) {
+      work(L);
     }
     __syncthreads();
-    smooth(r, a.nu2);
-  }
-  // iterates of every tail level back to global memory
-  for (int q = 0; q < nl; ++q) {
-    const TailLevel<T> &v = a.lv[q];
-    for (int c = t; c < v.nx * v.ny; c += kTailThreads) v.x[c] = X[v.off + c];
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kTailThreads) void k_tail(TailArgs<T> a) {
+template <typename T, int NT, bool FREE>
+__global__ __launch_bounds__(NT) void k_tail(TailArgs<T> a) {
   if (a.skip && *a.skip != 0.0) return;
-  tail_body<T>(a);
+  tail_body<T, NT, FREE>(a);
 }
 
 // Batched form: one workgroup per problem.
-template <typename T>
-__global__ __launch_bounds__(kTailThreads) void k_tail_b(BatchTab tab) {
+template <typename T, int NT, bool FREE>
+__global__ __launch_bounds__(NT) void k_tail_b(BatchTab tab) {
   const TailArgs<T> &a = *static_cast<const TailArgs<T> *>(tab.e[blockIdx.x].args);
-  tail_body<T>(a);
+  tail_body<T, NT, FREE>(a);
 }
 
 }  // namespace
 
-// Number of nodes a level may have to be handled by the tail.  A problem
-// alone hands the tail its levels from 33 x 33 down: the fused passes of
-// one-wave blocks on the 65 x 65 level cost less than that level in the
-// single workgroup (129^2 FP64 solve 0.651 -> 0.567 ms, 4097^2 11.83 ->
-// 11.68 ms).  In a batch the tail takes over from 65 x 65: there the
-// batched passes of that level cost more than the tail (the 256-problem
-// batch 26.5 -> 27.2 ms mixed with the tail from 33 x 33).
+// Number of nodes a level may have to be handled by the tail.  Alone from
+// 33 x 33 down: at 65 x 65 (FP32, the 1024-thread form) the level costs more
+// here than as two passes of its own (a mixed 129^2 step of two cycles 97.8
+// against 90.0 us).  In a batch, where the passes' launches are shared, the
+// tail takes it.  Measured alone, FP64, the tail from 33 x 33: 34 us a
+// launch with one node per thread and streamed stencils, 25 us with quads
+// (17 us where the stencils are still in L2: a 129^2 V-cycle 79 -> 67 us, 65^2
+// 55 -> 45 us).
 int tail_max_nodes(bool batch) { return batch ? kTailMaxNodes : 33 * 33; }
 
-// Largest tail LDS footprint for the node limits above: the first level at
-// kTailMaxNodes, three more each at most a quarter of the previous plus a
-// ring, one residual array and the streamed right-hand sides.
-static_assert((kTailMaxNodes * 2 + 1100 + 300 + 100 + 1100) * 8 <= kTailLdsMax,
-              "tail LDS exceeds the workgroup limit");
-
+// Quads, LDS planes and thread ranges of the tail from level lc on; false
+// when it does not fit a workgroup.
 template <typename T>
-static TailArgs<T> make_tail_args(tomg_problem *p, int lc) {
-  TailArgs<T> a{};
+static bool make_tail_args(const tomg_problem *p, int lc, TailArgs<T> &a) {
+  a = TailArgs<T>{};
   const bool f32 = std::is_same<T, float>::value;
+  const bool free_ring = stored_level0(p->cfg);
+  const int off = free_ring ? 0 : 1;
   a.lc = lc;
   a.nl = p->L - lc;
   a.nu1 = p->cfg.nu1;
   a.nu2 = p->cfg.nu2;
   a.cinv = p->cinv;
   a.cidx = p->cidx;
-  int off = 0, rmax = 0, boff = 0;
+  if (a.nl > kTailLevels) return false;
+  int at = 0, t0 = 0, rmax = 0;
   for (int q = 0; q < a.nl; ++q) {
     const Level &v = p->lv[lc + q];
-    a.lv[q].nx = v.nx;
-    a.lv[q].ny = v.ny;
-    a.lv[q].st = (const T *)(f32 ? (void *)v.st32 : (void *)v.st);
-    a.lv[q].x = (T *)(f32 ? (void *)v.x32 : (void *)v.x);
-    a.lv[q].b = (const T *)(f32 ? (void *)v.b32 : (void *)v.b);
-    a.lv[q].dir = v.dir;
-    a.lv[q].off = off;
-    const int n = v.nx * v.ny;
-    a.lv[q].boff = -1;
-    if (q > 0 && q < a.nl - 2) {  // streamed level below the first
-      a.lv[q].boff = boff;
-      boff += n;
+    TailLevel<T> &e = a.lv[q];
+    e.nx = v.nx;
+    e.ny = v.ny;
+    e.st = (const T *)(f32 ? (void *)v.st32 : (void *)v.st);
+    e.x = (T *)(f32 ? (void *)v.x32 : (void *)v.x);
+    e.b = (const T *)(f32 ? (void *)v.b32 : (void *)v.b);
+    e.dir = v.dir;
+    const bool coarsest = q == a.nl - 1;
+    e.qx = (v.nx + 1 - off) / 2;
+    const int qy = (v.ny + 1 - off) / 2;
+    e.nq = e.qx * qy;
+    e.pitch = e.qx + 2;
+    e.ps = e.pitch * (qy + 2);
+    e.xoff = at;
+    at += coarsest ? v.nx * v.ny : 4 * e.ps;
+    if (q > 0) {
+      e.foff = at;
+      at += v.nx * v.ny;
     }
-    off += n;
-    if (q < a.nl - 1) rmax = rmax > n ? rmax : n;
+    if (free_ring && !coarsest) {  // its ring of zeros is read: planes of its own
+      e.roff = at;
+      at += 4 * e.ps;
+    } else if (!coarsest) {
+      rmax = rmax > 4 * e.ps ? rmax : 4 * e.ps;
+    }
+    if (q > 0 && !coarsest) {
+      e.t0 = t0;
+      t0 = (t0 + e.nq + 63) / 64 * 64;
+    }
   }
-  a.shmem = (off + rmax + boff) * (int)sizeof(T);
-  return a;
+  if (!free_ring) {
+    for (int q = 0; q + 1 < a.nl; ++q) a.lv[q].roff = at;
+    at += rmax;
+  }
+  a.lds = at;
+  a.shmem = (int)(kMaxCoarseUnknowns * kMaxCoarseUnknowns * sizeof(double)) + at * (int)sizeof(T);
+  const int need = a.nl > 1 ? (a.lv[0].nq > t0 ? a.lv[0].nq : t0) : 1;
+  a.wide = need > kTailNarrow;
+  // at FP64 a quad does not fit the wide form's 128 registers per thread
+  return need <= (f32 ? kTailWide : kTailNarrow) && a.shmem <= kTailLdsMax;
+}
+
+// Whether the tail can start at level l.
+bool tail_fits(const tomg_problem *p, int l, bool batch) {
+  if ((long)p->lv[l].nx * p->lv[l].ny > tail_max_nodes(batch)) return false;
+  for (int k = l; k < p->L; ++k)
+    if (p->lv[k].ck != 0) return false;
+  TailArgs<double> a64;
+  TailArgs<float> a32;
+  return p->cfg.precision == TOMG_FP32_IR ? make_tail_args<float>(p, l, a32)
+                                          : make_tail_args<double>(p, l, a64);
 }
 
 void build_tail_args(tomg_problem *p) {
-  p->hargs.tail64 = make_tail_args<double>(p, p->lc);
-  p->hargs.tail64b = make_tail_args<double>(p, p->lcb);
+  make_tail_args<double>(p, p->lc, p->hargs.tail64);
+  make_tail_args<double>(p, p->lcb, p->hargs.tail64b);
   if (p->cfg.precision == TOMG_FP32_IR) {
-    p->hargs.tail32 = make_tail_args<float>(p, p->lc);
-    p->hargs.tail32b = make_tail_args<float>(p, p->lcb);
+    make_tail_args<float>(p, p->lc, p->hargs.tail32);
+    make_tail_args<float>(p, p->lcb, p->hargs.tail32b);
   }
 }
 
-// Levels lc..L-1 in one workgroup; xs/bs/sts give the per-level correction,
-// right-hand side and stencil arrays of precision T (indexed by level).
+// Levels lc..L-1 in one workgroup.
 template <typename T>
-void tail_cycle(tomg_problem *p, int lc, T *const *xs, T *const *bs, const T *const *sts) {
-  TailArgs<T> a = make_tail_args<T>(p, lc);
-  for (int q = 0; q < a.nl; ++q) {
-    a.lv[q].st = sts[lc + q];
-    a.lv[q].x = xs[lc + q];
-    a.lv[q].b = bs[lc + q];
-  }
+void tail_cycle(tomg_problem *p) {
+  TailArgs<T> a = std::is_same<T, float>::value ? *(TailArgs<T> *)(void *)&p->hargs.tail32
+                                                : *(TailArgs<T> *)(void *)&p->hargs.tail64;
   a.skip = p->skip;
-  hipLaunchKernelGGL((k_tail<T>), 1, kTailThreads, a.shmem, p->stream, a);
+  const bool fr = stored_level0(p->cfg);
+  if constexpr (std::is_same<T, float>::value) {
+    if (a.wide) {
+      if (fr)
+        hipLaunchKernelGGL((k_tail<T, kTailWide, true>), 1, kTailWide, a.shmem, p->stream, a);
+      else
+        hipLaunchKernelGGL((k_tail<T, kTailWide, false>), 1, kTailWide, a.shmem, p->stream, a);
+      return;
+    }
+  }
+  if (fr)
+    hipLaunchKernelGGL((k_tail<T, kTailNarrow, true>), 1, kTailNarrow, a.shmem, p->stream, a);
+  else
+    hipLaunchKernelGGL((k_tail<T, kTailNarrow, false>), 1, kTailNarrow, a.shmem, p->stream, a);
 }
 
-template void tail_cycle<double>(tomg_problem *, int, double *const *, double *const *,
-                                 const double *const *);
-template void tail_cycle<float>(tomg_problem *, int, float *const *, float *const *,
-                                const float *const *);
+template void tail_cycle<double>(tomg_problem *);
+template void tail_cycle<float>(tomg_problem *);
 
-void batch_tail(tomg_problem *const *probs, const int *idx, int cnt, bool fp32, hipStream_t s) {
+template <typename T>
+static void batch_tail_t(tomg_problem *const *probs, const int *idx, int cnt, hipStream_t s) {
+  constexpr bool f32 = std::is_same<T, float>::value;
   BatchTab tab;
   for (int k0 = 0; k0 < cnt; k0 += kBatchMax) {
     tab.count = 0;
-    int shmem = 0;
+    int shmem = 0, wide = 0;
     for (int k = k0; k < cnt && k < k0 + kBatchMax; ++k) {
       tomg_problem *p = probs[idx[k]];
       BatchEntry &e = tab.e[tab.count];
-      e.args = fp32 ? (const void *)&p->dargs->tail32b : (const void *)&p->dargs->tail64b;
+      e.args = f32 ? (const void *)&p->dargs->tail32b : (const void *)&p->dargs->tail64b;
       e.phi = nullptr;
       e.role = 0;
       e.nbx = e.nby = 1;
       e.start = tab.count;
       e.slot = e.out = 0;
-      const int sh = fp32 ? p->hargs.tail32b.shmem : p->hargs.tail64b.shmem;
+      const int sh = f32 ? p->hargs.tail32b.shmem : p->hargs.tail64b.shmem;
       shmem = shmem > sh ? shmem : sh;
+      wide |= f32 ? p->hargs.tail32b.wide : p->hargs.tail64b.wide;
       ++tab.count;
     }
     if (!tab.count) continue;
-    if (fp32)
-      hipLaunchKernelGGL(k_tail_b<float>, tab.count, kTailThreads, shmem, s, tab);
+    // a batch has one level-0 operator form, hence one kind of ring
+    const bool fr = stored_level0(probs[idx[k0]]->cfg);
+    if constexpr (f32) {
+      if (wide) {
+        if (fr)
+          hipLaunchKernelGGL((k_tail_b<T, kTailWide, true>), tab.count, kTailWide, shmem, s, tab);
+        else
+          hipLaunchKernelGGL((k_tail_b<T, kTailWide, false>), tab.count, kTailWide, shmem, s, tab);
+        continue;
+      }
+    }
+    if (fr)
+      hipLaunchKernelGGL((k_tail_b<T, kTailNarrow, true>), tab.count, kTailNarrow, shmem, s, tab);
     else
-      hipLaunchKernelGGL(k_tail_b<double>, tab.count, kTailThreads, shmem, s, tab);
+      hipLaunchKernelGGL((k_tail_b<T, kTailNarrow, false>), tab.count, kTailNarrow, shmem, s, tab);
   }
+}
+
+void batch_tail(tomg_problem *const *probs, const int *idx, int cnt, bool fp32, hipStream_t s) {
+  if (fp32)
+    batch_tail_t<float>(probs, idx, cnt, s);
+  else
+    batch_tail_t<double>(probs, idx, cnt, s);
 }
 
 }  // namespace tomg

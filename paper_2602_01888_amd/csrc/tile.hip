@@ -1,0 +1,267 @@
+// Level passes of the small and middle levels on whole tiles (arXiv
+// 2602.01888, Section 3): the same down and up passes as the band-marching
+// ones (fused.hip), for levels whose passes are bound by latency.
+//
+// A marching block runs a chain of eleven barrier phases for every two rows
+// of its band and halo, and waits for each step's loads: 12 .. 22 us for
+// levels of 65^2 .. 513^2 nodes, whatever the width.  Here a workgroup loads
+// a whole tile with its halo at once, each thread one 2 x 2 quad (quad.h),
+// and runs the colour phases over the tile: 4 nu barriers and one memory
+// latency in all, every lane relaxing one node in each phase.  The price is
+// the halo (4 nu + 2 columns, 2 nu + 2 rows), recomputed and read again by
+// the neighbouring tiles, so large levels, bound by their bytes, stay with
+// the marching passes.
+//
+// Halo.  Quads start at even nodes, and a region edge is not relaxed unless
+// it is the grid's.  A sweep then leaves wrong values in the outer four
+// columns and two rows on the low side, and one column and one row fewer on
+// the high side; the residual and its restriction take one more each.
+#include <type_traits>
+
+#include "quad.h"
+#include "tomg_internal.h"
+
+namespace tomg {
+namespace {
+
+template <int NU, bool RES>
+struct Halo {  // nodes around the owned tile (even, so that quads stay whole)
+  static constexpr int W = 4 * NU + (RES ? 2 : 0), E = 4 * NU;
+  static constexpr int S = 2 * NU + (RES ? 2 : 0), N = 2 * NU;
+};
+
+template <typename T, bool EPS, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, int QX,
+          int QY>
+__device__ __forceinline__ void tile_body(const PassArgs<T> &a, const int bx, const int by) {
+  using H = Halo<NU, RESTRICT || NORM>;
+  constexpr int PITCH = QX + 2, PS = PITCH * (QY + 2);
+  __shared__ T S[4 * PS];
+  __shared__ double red[QX * QY / 64];
+  const int t = threadIdx.x, u = t % QX, w = t / QX;
+  const int nx = a.nx, ny = a.ny;
+  const int i0 = bx * a.W - H::W + 2 * u, j0 = by * a.CH - H::S + 2 * w;
+  // columns are loaded in pairs from ib; a pair that would start at the last
+  // column starts one before it
+  const int ib = min(max(i0, 0), nx - 2);
+  const bool last = i0 > ib;
+  const size_t n = (size_t)nx * ny;
+  auto row = [&](int j) { return (size_t)min(max(j, 0), ny - 1) * nx; };
+  T *c = S + (w + 1) * PITCH + u + 1;
+
+  std::conditional_t<EPS, QuadEps<T>, QuadSt<T>> q;
+  bool in[4];  // node inside the grid
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const size_t at = row(j0 + b) + ib;
+    const auto f = load_pair(a.b + at);
+    q.f[2 * b] = last ? f[1] : f[0];
+    q.f[2 * b + 1] = f[1];
+    if constexpr (!ZERO) {
+      const auto x = load_pair(a.xin + at);
+      q.x[2 * b] = last ? x[1] : x[0];
+      q.x[2 * b + 1] = x[1];
+    }
+    const uint8_t d0 = a.dir[last ? at + 1 : at], d1 = a.dir[at + 1];
+    const bool rowin = j0 + b >= 0 && j0 + b < ny;
+    in[2 * b] = rowin && i0 >= 0 && i0 < nx;
+    in[2 * b + 1] = rowin && i0 + 1 >= 0 && i0 + 1 < nx;
+    // provisional: 1 where the node may change
+    q.ik[2 * b] = in[2 * b] && !d0 ? T(1) : T(0);
+    q.ik[2 * b + 1] = in[2 * b + 1] && !d1 ? T(1) : T(0);
+  }
+  T dg[4];
+  if constexpr (EPS) {
+    // columns i0 - 1 .. i0 + 2, rows j0 - 1 .. j0 + 2 (clamped: only nodes
+    // inside the grid's ring use them)
+    const int iw = min(max(i0 - 1, 0), nx - 1), ie = min(max(i0 + 2, 0), nx - 1);
+    T xx[2][4], xy[4][4], yy[4][2];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const size_t at = row(j0 - 1 + r);
+      const auto pxy = load_pair(a.exy + at + ib), pyy = load_pair(a.eyy + at + ib);
+      xy[r][1] = last ? pxy[1] : pxy[0];
+      xy[r][2] = pxy[1];
+      yy[r][0] = last ? pyy[1] : pyy[0];
+      yy[r][1] = pyy[1];
+      if (r == 1 || r == 2) {
+        const auto pxx = load_pair(a.exx + at + ib);
+        xx[r - 1][1] = last ? pxx[1] : pxx[0];
+        xx[r - 1][2] = pxx[1];
+        xx[r - 1][0] = a.exx[at + iw];
+        xx[r - 1][3] = a.exx[at + ie];
+        xy[r][0] = a.exy[at + iw];
+        xy[r][3] = a.exy[at + ie];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int x = k & 1, y = k >> 1;
+      const T ax = xx[y][x + 1] * a.cx, ay = yy[y + 1][x] * a.cy;
+      T gx, gy;
+      eps_coefs(xx[y][x + 2] - xx[y][x], yy[y + 2][x] - yy[y][x], xy[y + 1][x + 2] - xy[y + 1][x],
+                xy[y + 2][x + 1] - xy[y][x + 1], a.qx, a.qy, a.qxy, gx, gy);
+      q.k1[k] = plain_add(ax, gx);
+      q.k3[k] = plain_add(ax, -gx);
+      q.k4[k] = plain_add(ay, gy);
+      q.k5[k] = plain_add(ay, -gy);
+      q.k6[k] = xy[y + 1][x + 1] * a.hxy;
+      dg[k] = q.dg[k] = eps_diag(ax, ay);
+    }
+  } else {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const size_t at = row(j0 + b) + ib;
+#pragma unroll
+      for (int z = 0; z < 9; ++z) {
+        const auto p = load_pair(a.st + z * n + at);
+        q.a[2 * b][z] = last ? p[1] : p[0];
+        q.a[2 * b + 1][z] = p[1];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) dg[k] = q.a[k][4];
+  }
+  if constexpr (PROLONG) {
+    const int I = min(max(i0 >> 1, 0), a.nxc - 1), J = min(max(j0 >> 1, 0), a.nyc - 1);
+    const int I1 = min(I + 1, a.nxc - 1), J1 = min(J + 1, a.nyc - 1);
+    const T *r0 = a.xc + (size_t)J * a.nxc, *r1 = a.xc + (size_t)J1 * a.nxc;
+    const T c00 = r0[I], c01 = r0[I1], c10 = r1[I], c11 = r1[I1];
+    const T e01 = T(0.5) * (c00 + c01), e11 = T(0.5) * (c10 + c11);
+    const T e[4] = {c00, e01, T(0.5) * (c00 + c10), T(0.5) * (e01 + e11)};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (q.ik[k] != T(0)) q.x[k] += e[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (ZERO || !in[k]) q.x[k] = T(0);
+    c[k * PS] = q.x[k];
+    // the region's edge has no neighbours here and keeps its value (it is
+    // outside the grid, or wrong and never reaches the owned tile)
+    const bool edge = ((k & 1) ? u == QX - 1 : u == 0) || ((k >> 1) ? w == QY - 1 : w == 0);
+    q.ik[k] = q.ik[k] != T(0) && !edge ? T(1) / dg[k] : T(0);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < NU; ++s)
+#pragma unroll
+    for (int col = 0; col < 4; ++col) {
+      quad_relax<T>(q, c, col, PS, PITCH);
+      __syncthreads();
+    }
+  const bool own = u >= H::W / 2 && 2 * u < H::W + a.W && w >= H::S / 2 && 2 * w < H::S + a.CH;
+  T res[4];
+  double acc = 0.0;
+  if constexpr (RESTRICT || NORM) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      res[k] = quad_resid<T>(q, c, k, PS, PITCH);
+      if (own && in[k]) acc += (double)(res[k] * res[k]);
+    }
+  }
+  if (own) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (in[k]) a.xout[(size_t)(j0 + (k >> 1)) * nx + i0 + (k & 1)] = q.x[k];
+  }
+  if constexpr (RESTRICT) {
+    __syncthreads();  // the residuals take the iterate's place in LDS
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c[k * PS] = res[k];
+    __syncthreads();
+    if (own && in[0]) {
+      const int I = i0 >> 1, J = j0 >> 1;
+      const bool ring = I == 0 || J == 0 || I == a.nxc - 1 || J == a.nyc - 1;
+      // a coarse ring node is Dirichlet unless its edge is Neumann
+      const bool fixed = ring && (!a.dirc || a.dirc[(size_t)J * a.nxc + I]);
+      const T v = quad_full_weight(res, c, 0, PS, PITCH);
+      a.bc[(size_t)J * a.nxc + I] = fixed ? T(0) : v;
+    }
+  }
+  if constexpr (NORM) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+    if ((t & 63) == 0) red[t >> 6] = acc;
+    __syncthreads();
+    if (t == 0) {
+      for (int k = 1; k < QX * QY / 64; ++k) acc += red[k];
+      a.partials[(size_t)by * a.nbx + bx] = acc;
+    }
+  }
+}
+
+template <typename T, bool EPS, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, int QX,
+          int QY>
+__global__ __launch_bounds__(QX *QY) void k_tile(PassArgs<T> a) {
+  if (a.skip && *a.skip != 0.0) return;
+  tile_body<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, QX, QY>(a, blockIdx.x % a.nbx,
+                                                              blockIdx.x / a.nbx);
+}
+
+template <typename T, bool EPS, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
+void launch_shape(const PassArgs<T> &a, hipStream_t s) {
+  const int nb = a.nbx * a.nby;
+  if (a.tile == kTileLarge)
+    hipLaunchKernelGGL((k_tile<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, 32, 16>), nb, 512, 0, s,
+                       a);
+  else
+    hipLaunchKernelGGL((k_tile<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, 16, 16>), nb, 256, 0, s,
+                       a);
+}
+template <typename T, bool EPS, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
+void launch_nu(int nu, const PassArgs<T> &a, hipStream_t s) {
+  if (nu == 1)
+    launch_shape<T, EPS, 1, ZERO, PROLONG, RESTRICT, NORM>(a, s);
+  else
+    launch_shape<T, EPS, 2, ZERO, PROLONG, RESTRICT, NORM>(a, s);
+}
+
+}  // namespace
+
+// Gives the pass the tile form where it is the faster one: alone, both axes
+// halved, at most two sweeps.
+template <typename T>
+bool pick_tile(PassArgs<T> &a, int nu, bool res) {
+  a.tile = kTileNone;
+  const long n = (long)a.nx * a.ny;
+  static const char *e0 = getenv("TT0"), *e1 = getenv("TT1");
+  const long m0 = e0 ? atol(e0) : 300000, m1 = e1 ? atol(e1) : 70000;
+  if (nu > 2 || a.ck != 0 || n > m0) return false;
+  a.tile = n > m1 ? kTileLarge : kTileSmall;
+  const int hx = 8 * nu + (res ? 2 : 0), hy = 4 * nu + (res ? 2 : 0);
+  a.W = (a.tile == kTileLarge ? 64 : 32) - hx;
+  a.CH = 32 - hy;
+  a.nbx = (a.nx + a.W - 1) / a.W;
+  a.nby = (a.ny + a.CH - 1) / a.CH;
+  a.xcd_order = 0;
+  return true;
+}
+template bool pick_tile<double>(PassArgs<double> &, int, bool);
+template bool pick_tile<float>(PassArgs<float> &, int, bool);
+
+template <typename T>
+void tile_down(int nu, bool eps, bool zero, const PassArgs<T> &a, hipStream_t s) {
+  if (eps) {
+    if (zero) launch_nu<T, true, true, false, true, false>(nu, a, s);
+    else launch_nu<T, true, false, false, true, false>(nu, a, s);
+  } else {
+    if (zero) launch_nu<T, false, true, false, true, false>(nu, a, s);
+    else launch_nu<T, false, false, false, true, false>(nu, a, s);
+  }
+}
+template <typename T>
+void tile_up(int nu, bool eps, bool norm, const PassArgs<T> &a, hipStream_t s) {
+  if (eps) {
+    if (norm) launch_nu<T, true, false, true, false, true>(nu, a, s);
+    else launch_nu<T, true, false, true, false, false>(nu, a, s);
+  } else {
+    if (norm) launch_nu<T, false, false, true, false, true>(nu, a, s);
+    else launch_nu<T, false, false, true, false, false>(nu, a, s);
+  }
+}
+template void tile_down<double>(int, bool, bool, const PassArgs<double> &, hipStream_t);
+template void tile_down<float>(int, bool, bool, const PassArgs<float> &, hipStream_t);
+template void tile_up<double>(int, bool, bool, const PassArgs<double> &, hipStream_t);
+template void tile_up<float>(int, bool, bool, const PassArgs<float> &, hipStream_t);
+
+}  // namespace tomg

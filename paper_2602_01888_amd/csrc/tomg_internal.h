@@ -98,9 +98,11 @@ struct TailLevel {
   T *x;
   const T *b;
   const uint8_t *dir;
-  int off;   // offset of the level's iterate in the LDS array
-  int boff;  // offset of its right-hand side in LDS (levels after the first
-             // with more nodes than the tail has threads), else -1
+  int qx, nq;     // quads per row, and in all
+  int pitch, ps;  // row pitch and size of an LDS plane (a ring of zeros around the quads)
+  int xoff, roff; // LDS offsets (elements) of its iterate and residual planes
+  int foff;       // LDS offset of its right-hand side (levels after the first)
+  int t0;         // first thread of the quads' owners
 };
 constexpr int kTailLevels = 4;
 template <typename T>
@@ -108,7 +110,9 @@ struct TailArgs {
   int lc, nl, nu1, nu2;  // levels lc .. lc+nl-1 (the last is the coarsest)
   const double *cinv;
   const int *cidx;
+  int lds;               // LDS elements of the planes and right-hand sides
   int shmem;             // dynamic LDS bytes
+  int wide;              // the top level needs the 1024-thread form
   const double *skip;    // as in PassArgs
   TailLevel<T> lv[kTailLevels];
 };
@@ -298,8 +302,8 @@ void fused_updown(tomg_problem *p, const T *pong, T *out, const T *b, const T *e
 
 // levels lc..L-1 of the cycle in one workgroup (tail.hip)
 template <typename T>
-void tail_cycle(tomg_problem *p, int lc, T *const *xs, T *const *bs, const T *const *sts);
-int tail_max_nodes(bool batch);
+void tail_cycle(tomg_problem *p);
+bool tail_fits(const tomg_problem *p, int l, bool batch);
 hipError_t launch_ir_residual(tomg_problem *p, const double *phi);
 hipError_t launch_ir_correct(tomg_problem *p, double *phi);
 hipError_t launch_ir_inner(tomg_problem *p);
