@@ -63,7 +63,8 @@ constexpr int kBW = TOMG_BW;
 constexpr int kBWSmall = 64;
 constexpr int kBWWide = 256;
 constexpr int kBWBatch = TOMG_BW_BATCH;
-constexpr long kSmallPassNodes = 2L << 20;  // largest level given one-wave blocks
+constexpr long kSmallPassNodes = 2L << 20;  // largest level given one-wave blocks (where
+                                            // it does not run on tiles, tile.hip)
 
 // Streaming stores: the pass outputs are read back by the next pass, long
 // after the caches have turned over, so they are written with the
@@ -839,6 +840,9 @@ static PassArgs<T> make_args(tomg_problem *p, int l, bool up, bool batch, T *x0,
   const int nu = up ? p->cfg.nu2 : p->cfg.nu1;
   const bool small = !batch && (l > 0 || stored) && v.ck == 0 &&
                      (long)a.nx * a.ny <= kSmallPassNodes;
+  a.ck = v.ck;
+  // the residual follows the sweeps in a down pass and where the norm is taken
+  if (!batch && pick_tile(a, nu, !up || (l == 0 && !f32))) return a;
   a.bw = batch ? kBWBatch : (small ? kBWSmall : kBW);
   a.W = a.bw - 2 * (4 * nu + 2);
   a.CH = batch ? pick_band_batch(a.nx, a.ny, a.W)
@@ -846,7 +850,6 @@ static PassArgs<T> make_args(tomg_problem *p, int l, bool up, bool batch, T *x0,
   a.nbx = (a.nx + a.W - 1) / a.W;
   a.nby = (a.ny + a.CH - 1) / a.CH;
   a.xcd_order = (!batch && a.nbx > 1) ? 1 : 0;
-  a.ck = v.ck;
   return a;
 }
 
@@ -887,6 +890,7 @@ void build_pass_args(tomg_problem *p) {
     a.nbx = (a.nx + a.W - 1) / a.W;
     a.nby = (a.ny + a.CH - 1) / a.CH;
     a.xcd_order = a.nbx > 1 ? 1 : 0;
+    a.tile = kTileNone;
     g.updown32 = a;
   }
 }
@@ -894,6 +898,7 @@ void build_pass_args(tomg_problem *p) {
 template <typename T>
 static void launch_down(int nu, bool eps, bool zero, const PassArgs<T> &a, hipStream_t s,
                         const BatchTab *tab, int nb) {
+  if (!tab && a.tile) return tile_down<T>(nu, eps, zero, a, s);
   if (eps) {
     if (zero) launch_pass<T, true, true, false, true, false>(nu, a, s, tab, nb);
     else launch_pass<T, true, false, false, true, false>(nu, a, s, tab, nb);
@@ -906,6 +911,7 @@ static void launch_down(int nu, bool eps, bool zero, const PassArgs<T> &a, hipSt
 template <typename T>
 static void launch_up(int nu, bool eps, bool norm, const PassArgs<T> &a, hipStream_t s,
                       const BatchTab *tab, int nb) {
+  if (!tab && a.tile) return tile_up<T>(nu, eps, norm, a, s);
   if (eps) {
     if (norm) launch_pass<T, true, false, true, false, true>(nu, a, s, tab, nb);
     else launch_pass<T, true, false, true, false, false>(nu, a, s, tab, nb);

@@ -20,20 +20,20 @@ namespace tomg {
 // the fused one depends on where its operands live, and a problem solved
 // alone and in a batch, by different kernels, must agree bit for bit.
 
-// f minus the off-centre part of a stored 9-point stencil (two chains of
-// four multiply-adds: half the latency of one of eight).
+// f minus the off-centre part of a stored 9-point stencil.
 template <typename T>
 __device__ __forceinline__ T defect9(T f, const T *a, T sw, T s, T se, T w, T e, T nw, T n,
                                      T ne) {
 #pragma clang fp contract(off)
-  T p = __builtin_elementwise_fma(-a[0], sw, f), q = a[5] * e;
-  p = __builtin_elementwise_fma(-a[1], s, p);
-  q = __builtin_elementwise_fma(a[6], nw, q);
-  p = __builtin_elementwise_fma(-a[2], se, p);
-  q = __builtin_elementwise_fma(a[7], n, q);
-  p = __builtin_elementwise_fma(-a[3], w, p);
-  q = __builtin_elementwise_fma(a[8], ne, q);
-  return p - q;
+  T o = a[1] * s;
+  o = __builtin_elementwise_fma(a[0], sw, o);
+  o = __builtin_elementwise_fma(a[2], se, o);
+  o = __builtin_elementwise_fma(a[3], w, o);
+  o = __builtin_elementwise_fma(a[5], e, o);
+  o = __builtin_elementwise_fma(a[6], nw, o);
+  o = __builtin_elementwise_fma(a[7], n, o);
+  o = __builtin_elementwise_fma(a[8], ne, o);
+  return f - o;
 }
 // The same for eq. 18: k1, k3, k4, k5 the E, W, N, S neighbours, k6 the
 // diagonal difference.
@@ -41,12 +41,12 @@ template <typename T>
 __device__ __forceinline__ T defect18(T f, T k1, T k3, T k4, T k5, T k6, T sw, T s, T se, T w,
                                       T e, T nw, T n, T ne) {
 #pragma clang fp contract(off)
-  const T x = (ne - nw) - (se - sw);
-  T p = __builtin_elementwise_fma(-k1, e, f), q = k4 * n;
-  p = __builtin_elementwise_fma(-k3, w, p);
-  q = __builtin_elementwise_fma(k5, s, q);
-  q = __builtin_elementwise_fma(k6, x, q);
-  return p - q;
+  T o = k3 * w;
+  o = __builtin_elementwise_fma(k1, e, o);
+  o = __builtin_elementwise_fma(k4, n, o);
+  o = __builtin_elementwise_fma(k5, s, o);
+  o = __builtin_elementwise_fma(k6, (ne - nw) - (se - sw), o);
+  return f - o;
 }
 template <typename T>
 __device__ __forceinline__ T relaxed(T defect, T ik) { return defect * ik; }
@@ -62,7 +62,7 @@ template <typename T>
 __device__ __forceinline__ void eps_coefs(T dxx, T dyy, T xyx, T xyy, T qx, T qy, T qxy, T &gx,
                                           T &gy) {
 #pragma clang fp contract(off)
-  gx = __builtin_elementwise_fma(dxx, qx, xyy * qxy);
+  gx = __builtin_elementwise_fma(xyy, qxy, dxx * qx);
   gy = __builtin_elementwise_fma(dyy, qy, xyx * qxy);
 }
 template <typename T>

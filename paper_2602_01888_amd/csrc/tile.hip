@@ -219,15 +219,23 @@ void launch_nu(int nu, const PassArgs<T> &a, hipStream_t s) {
 }  // namespace
 
 // Gives the pass the tile form where it is the faster one: alone, both axes
-// halved, at most two sweeps.
+// halved, at most two sweeps (the halo of four is wider than the tile).
+// Measured per pass (down, up; V(2,2), FP64, a cycle of 4097^2), marching
+// -> tiles: 65^2 13.1, 14.1 -> 5.8, 5.3 us; 129^2 12.9, 12.4 -> 6.2, 5.8;
+// 257^2 14.7, 16.4 -> 7.9, 6.2; 513^2 21.7, 22.0 -> 15.7, 12.6; 1025^2 39.1,
+// 38.7 -> 36.4, 36.4.  At 2049^2 the two are even (a cycle of a 2049^2
+// problem 295 -> 305 us, FP32 470 -> 464), and the level-0 passes of 4097^2
+// are slower (310 against 240 us a pass).  Up to 257^2 the 32 x 32 tiles
+// give the device enough blocks (513^2 with them: a 513^2 cycle 71.5 -> 77.7
+// us); below, both sizes measure the same.
+constexpr long kTileNodes = 1200000;      // largest level on tiles
+constexpr long kSmallTileNodes = 70000;   // largest level on 32 x 32 tiles
 template <typename T>
 bool pick_tile(PassArgs<T> &a, int nu, bool res) {
   a.tile = kTileNone;
   const long n = (long)a.nx * a.ny;
-  static const char *e0 = getenv("TT0"), *e1 = getenv("TT1");
-  const long m0 = e0 ? atol(e0) : 300000, m1 = e1 ? atol(e1) : 70000;
-  if (nu > 2 || a.ck != 0 || n > m0) return false;
-  a.tile = n > m1 ? kTileLarge : kTileSmall;
+  if (nu > 2 || a.ck != 0 || n > kTileNodes) return false;
+  a.tile = n > kSmallTileNodes ? kTileLarge : kTileSmall;
   const int hx = 8 * nu + (res ? 2 : 0), hy = 4 * nu + (res ? 2 : 0);
   a.W = (a.tile == kTileLarge ? 64 : 32) - hx;
   a.CH = 32 - hy;

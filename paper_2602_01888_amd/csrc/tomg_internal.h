@@ -64,6 +64,10 @@ struct Level {
 
 // ---- per-problem launch arguments (device copies live in the workspace) ----
 
+// Forms of a level pass: a march up bands (fused.hip), or whole tiles of
+// 64 x 32 or 32 x 32 nodes, halo included (tile.hip).
+enum { kTileNone = 0, kTileSmall = 1, kTileLarge = 2 };
+
 // One fused level pass (fused.hip).
 template <typename T>
 struct PassArgs {
@@ -86,6 +90,7 @@ struct PassArgs {
   int xcd_order;             // tiles in XCD-contiguous order (one-dimensional grid)
   int ck;                    // transfer to the coarse level: 0 both axes halved, 1 x, 2 y
   int bw;                    // threads (columns) per block
+  int tile;                  // kTile*: the pass runs on whole tiles of CH x W owned nodes
   const double *skip;        // nonzero *skip: the launch does nothing (solve()
                              // queues cycles past convergence as no-ops)
 };
@@ -299,6 +304,15 @@ bool chain_inner(const tomg_problem *p);
 template <typename T>
 void fused_updown(tomg_problem *p, const T *pong, T *out, const T *b, const T *exx,
                   const T *exy, const T *eyy, const T *st, const T *xc, T *bc);
+
+// the same passes on whole tiles (tile.hip): pick_tile sets a's form and
+// blocking (res: the pass forms residuals), the others launch it
+template <typename T>
+bool pick_tile(PassArgs<T> &a, int nu, bool res);
+template <typename T>
+void tile_down(int nu, bool eps, bool zero, const PassArgs<T> &a, hipStream_t s);
+template <typename T>
+void tile_up(int nu, bool eps, bool norm, const PassArgs<T> &a, hipStream_t s);
 
 // levels lc..L-1 of the cycle in one workgroup (tail.hip)
 template <typename T>

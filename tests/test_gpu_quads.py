@@ -1,6 +1,7 @@
 """The quad kernels (one thread, one 2 x 2 quad of nodes) at the sizes where
 their blocking can go wrong: the single-workgroup tail with ragged, long and
-minimal levels, with a Dirichlet and with a free outer ring.  Two V-cycles and
+minimal levels, with a Dirichlet and with a free outer ring, and the tiled
+passes around their tile and threshold sizes.  Two V-cycles and
 every level's correction against the oracle's at the bounds of the
 other V-cycle tests (1e-12, 1e-11: a few hundred roundings), and a
 batch, whose levels run in other kernels, bitwise equal to solving alone."""
@@ -52,6 +53,16 @@ CASES = {
     "tail65_neumann": (_neumann, 65, 65, 2, 2),
     "tail97x49_neumann": (_neumann, 97, 49, 1, 2),
     "tail33x65_neumann": (_neumann, 33, 65, 3, 3),
+    # tiles: one tile wide (14 or 16 owned columns, 22 or 24 rows), one more
+    # column or row than whole tiles, both tile sizes, one and two sweeps
+    "tile5x9": (_sine, 5, 9, 2, 2),
+    "tile17x25": (_sine, 17, 25, 2, 2),
+    "tile113x89": (_sine, 113, 89, 2, 2),
+    "tile129_nu1": (_sine, 129, 129, 1, 1),
+    "tile257x273": (_sine, 257, 273, 2, 1),
+    "tile289x577": (_sine, 289, 577, 1, 2),
+    "tile161x145_neumann": (_neumann, 161, 145, 2, 2),
+    "tile321x257_neumann": (_neumann, 321, 257, 1, 1),
 }
 
 
