@@ -522,32 +522,6 @@ __device__ __forceinline__ void pass_body(const PassArgs<T> &a, const int bx, co
   }
 }
 
-// Odd bands march down (TOMG_MIRROR): then two neighbouring bands reach
-// their common boundary at the same time -- at the start of the pass for one
-// pair, at its end for the other -- and the halo rows both read are served
-// by the cache instead of being fetched from memory twice.  FP64 passes
-// only: the FP32 passes move half the bytes and gain nothing from it.
-#ifndef TOMG_MIRROR
-#define TOMG_MIRROR 1
-#endif
-template <typename T>
-__device__ __forceinline__ bool mirrored(int by, int ny) {
-  return TOMG_MIRROR && std::is_same<T, double>::value && (by & 1) && (ny & 1);
-}
-
-// Tile of a block of a one-dimensional launch.  Workgroups go to the eight
-// XCDs in turn (XCD = linear id mod 8); each XCD is given one contiguous run
-// of tiles in strip-fastest order, so the neighbouring strips of a band --
-// which read each other's halo columns at about the same time -- share that
-// XCD's L2 instead of fetching the halo twice from memory.
-__device__ __forceinline__ void xcd_tile(int id, int nbx, int nby, int &bx, int &by) {
-  const int n = nbx * nby, per = n >> 3, rem = n & 7;
-  const int xcd = id & 7, q = id >> 3;
-  const int tile = xcd * per + min(xcd, rem) + q;
-  bx = tile % nbx;
-  by = tile / nbx;
-}
-
 template <typename T, bool EPS, int NU, int P, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM,
           int CK = 0, int BW = kBW>
 __global__ __launch_bounds__(BW, TOMG_MIN_WAVES) void k_pass(PassArgs<T> a) {
@@ -560,16 +534,6 @@ __global__ __launch_bounds__(BW, TOMG_MIN_WAVES) void k_pass(PassArgs<T> a) {
     pass_body<T, EPS, NU, P, ZERO, PROLONG, RESTRICT, NORM, false, CK, BW>(a, bx, by);
 }
 
-// Entry of a batched launch holding block b (entries sorted by start).
-__device__ __forceinline__ const BatchEntry &batch_locate(const BatchTab &tab, int b) {
-  int lo = 0, hi = tab.count - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (tab.e[mid].start <= b) lo = mid; else hi = mid - 1;
-  }
-  return tab.e[lo];
-}
-
 // Batched form: each problem runs exactly the blocks it would run alone
 // (one transfer kind per launch: the problems of a batch share their
 // semi-coarsened levels).
@@ -577,9 +541,7 @@ template <typename T, bool EPS, int NU, int P, bool ZERO, bool PROLONG, bool RES
           int CK = 0>
 __global__ __launch_bounds__(kBWBatch, TOMG_MIN_WAVES) void k_pass_b(BatchTab tab) {
   const BatchEntry &e = batch_locate(tab, blockIdx.x);
-  PassArgs<T> a = *static_cast<const PassArgs<T> *>(e.args);
-  if (e.role == 1) a.xin = static_cast<const T *>(e.phi);
-  if (e.role == 2) a.xout = static_cast<T *>(e.phi);
+  const PassArgs<T> a = batch_args<T>(e);
   const int local = blockIdx.x - e.start, bx = local % e.nbx, by = local / e.nbx;
   if (mirrored<T>(by, a.ny))
     pass_body<T, EPS, NU, P, ZERO, PROLONG, RESTRICT, NORM, true, CK, kBWBatch>(a, bx, by);
@@ -609,14 +571,12 @@ __global__ __launch_bounds__(kBWBatch, TOMG_MIN_WAVES) void k_pass_b(BatchTab ta
 // table; on the serving stream (sides 129-2049) it raised the closed-loop
 // capacity by 6 %.
 constexpr int kMinBand = 2;
-static int pick_band_batch(int nx, int ny, int W) {
-  (void)nx;
-  (void)W;
+int pick_band_batch(int ny) {
   const int c = ny >= 1025 ? 40 : (ny >= 513 ? 32 : (ny >= 257 ? 24 : 16));
   return c < ny ? c : ny;
 }
 
-static int pick_band(int nx, int ny, int W, long slots, int hv) {
+int pick_band(int nx, int ny, int W, long slots, int hv) {
   const long bx = (nx + W - 1) / W;
   int CH = (long)nx * ny > (2L << 20) ? 3 * hv + (3 * hv & 1) : kMinBand;
   while (CH < ny && bx * ((ny + CH - 1) / CH) > slots) CH += 2;
@@ -647,6 +607,21 @@ static void launch_small(const PassArgs<T> &a, dim3 grid, hipStream_t s) {
                        dim3(kBWSmall), 0, s, a);
 }
 
+// Both axes halved: with the operator formed from the tensor and at most two
+// sweeps such a pass has another form (pick_march).
+template <typename T, bool EPS, int NU, int P, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
+static void launch_alone(const PassArgs<T> &a, dim3 grid, hipStream_t s) {
+  if constexpr (!EPS || NU > 2)
+    hipLaunchKernelGGL((k_pass<T, EPS, NU, P, ZERO, PROLONG, RESTRICT, NORM>), grid, dim3(kBW), 0,
+                       s, a);
+}
+template <typename T, bool EPS, int NU, int P, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
+static void launch_batch(int nblocks, hipStream_t s, const BatchTab &tab) {
+  if constexpr (!EPS || NU > 2)
+    hipLaunchKernelGGL((k_pass_b<T, EPS, NU, P, ZERO, PROLONG, RESTRICT, NORM>), dim3(nblocks),
+                       dim3(kBWBatch), 0, s, tab);
+}
+
 // Sweep count, pair count and transfer kind are compile-time; dispatch on
 // the runtime nu and a.ck (for a batched launch, that of its first problem:
 // every problem of a batch has the same transfer at a given level).
@@ -666,8 +641,7 @@ static void launch_pass(int nu, const PassArgs<T> &a, hipStream_t s, const Batch
       hipLaunchKernelGGL((k_pass_b<T, EPS, NU, P, ZERO, PROLONG, RESTRICT, NORM, 2>),           \
                          dim3(nblocks), dim3(kBWBatch), 0, s, *tab);                                  \
     else if (tab)                                                                                \
-      hipLaunchKernelGGL((k_pass_b<T, EPS, NU, P, ZERO, PROLONG, RESTRICT, NORM>),              \
-                         dim3(nblocks), dim3(kBWBatch), 0, s, *tab);                                  \
+      launch_batch<T, EPS, NU, P, ZERO, PROLONG, RESTRICT, NORM>(nblocks, s, *tab);              \
     else if (small)                                                                              \
       launch_small<T, EPS, NU, P, ZERO, PROLONG, RESTRICT, NORM>(a, grid, s);                   \
     else if (a.ck == 1)                                                                          \
@@ -677,8 +651,7 @@ static void launch_pass(int nu, const PassArgs<T> &a, hipStream_t s, const Batch
       hipLaunchKernelGGL((k_pass<T, EPS, NU, P, ZERO, PROLONG, RESTRICT, NORM, 2>), grid,       \
                          dim3(kBW), 0, s, a);                                                    \
     else                                                                                         \
-      hipLaunchKernelGGL((k_pass<T, EPS, NU, P, ZERO, PROLONG, RESTRICT, NORM>), grid,          \
-                         dim3(kBW), 0, s, a);                                                    \
+      launch_alone<T, EPS, NU, P, ZERO, PROLONG, RESTRICT, NORM>(a, grid, s);                    \
   } while (0)
   switch (nu) {
     case 1: TOMG_LAUNCH(1); break;
@@ -689,7 +662,7 @@ static void launch_pass(int nu, const PassArgs<T> &a, hipStream_t s, const Batch
 #undef TOMG_LAUNCH
 }
 
-static int device_cus() {
+int device_cus() {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -702,10 +675,11 @@ static int device_cus() {
 template <typename T, bool EPS, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, int BW = kBW>
 static int pass_blocks_per_cu(int nu) {
   constexpr int P = EPS ? TOMG_PAIRS_EPS : TOMG_PAIRS_ST;
+  constexpr int CK = EPS ? 1 : 0;  // up to two sweeps, only semi-coarsened passes have EPS here
   const void *f;
   switch (nu) {
-    case 1: f = reinterpret_cast<const void *>(k_pass<T, EPS, 1, P, ZERO, PROLONG, RESTRICT, NORM, 0, BW>); break;
-    case 2: f = reinterpret_cast<const void *>(k_pass<T, EPS, 2, P, ZERO, PROLONG, RESTRICT, NORM, 0, BW>); break;
+    case 1: f = reinterpret_cast<const void *>(k_pass<T, EPS, 1, P, ZERO, PROLONG, RESTRICT, NORM, CK, BW>); break;
+    case 2: f = reinterpret_cast<const void *>(k_pass<T, EPS, 2, P, ZERO, PROLONG, RESTRICT, NORM, CK, BW>); break;
     case 3: f = reinterpret_cast<const void *>(k_pass<T, EPS, 3, P, ZERO, PROLONG, RESTRICT, NORM, 0, BW>); break;
     default: f = reinterpret_cast<const void *>(k_pass<T, EPS, 4, P, ZERO, PROLONG, RESTRICT, NORM, 0, BW>); break;
   }
@@ -842,10 +816,11 @@ static PassArgs<T> make_args(tomg_problem *p, int l, bool up, bool batch, T *x0,
                      (long)a.nx * a.ny <= kSmallPassNodes;
   a.ck = v.ck;
   // the residual follows the sweeps in a down pass and where the norm is taken
-  if (!batch && pick_tile(a, nu, !up || (l == 0 && !f32))) return a;
+  if (pick_tile(a, nu, !up || (l == 0 && !f32), batch)) return a;
+  if (l == 0 && !stored && pick_march(a, nu, up, batch)) return a;
   a.bw = batch ? kBWBatch : (small ? kBWSmall : kBW);
   a.W = a.bw - 2 * (4 * nu + 2);
-  a.CH = batch ? pick_band_batch(a.nx, a.ny, a.W)
+  a.CH = batch ? pick_band_batch(a.ny)
               : pick_band(a.nx, a.ny, a.W, pass_slots<T>(l, up, nu, !stored, small), 2 * nu + 3);
   a.nbx = (a.nx + a.W - 1) / a.W;
   a.nby = (a.ny + a.CH - 1) / a.CH;
@@ -890,7 +865,7 @@ void build_pass_args(tomg_problem *p) {
     a.nbx = (a.nx + a.W - 1) / a.W;
     a.nby = (a.ny + a.CH - 1) / a.CH;
     a.xcd_order = a.nbx > 1 ? 1 : 0;
-    a.tile = kTileNone;
+    a.form = kFormBand;
     g.updown32 = a;
   }
 }
@@ -898,7 +873,8 @@ void build_pass_args(tomg_problem *p) {
 template <typename T>
 static void launch_down(int nu, bool eps, bool zero, const PassArgs<T> &a, hipStream_t s,
                         const BatchTab *tab, int nb) {
-  if (!tab && a.tile) return tile_down<T>(nu, eps, zero, a, s);
+  if (a.form == kFormMarch) return march_down<T>(nu, zero, a, s, tab, nb);
+  if (a.form != kFormBand) return tile_down<T>(nu, eps, zero, a, s, tab, nb);
   if (eps) {
     if (zero) launch_pass<T, true, true, false, true, false>(nu, a, s, tab, nb);
     else launch_pass<T, true, false, false, true, false>(nu, a, s, tab, nb);
@@ -911,7 +887,8 @@ static void launch_down(int nu, bool eps, bool zero, const PassArgs<T> &a, hipSt
 template <typename T>
 static void launch_up(int nu, bool eps, bool norm, const PassArgs<T> &a, hipStream_t s,
                       const BatchTab *tab, int nb) {
-  if (!tab && a.tile) return tile_up<T>(nu, eps, norm, a, s);
+  if (a.form == kFormMarch) return march_up<T>(nu, norm, a, s, tab, nb);
+  if (a.form != kFormBand) return tile_up<T>(nu, eps, norm, a, s, tab, nb);
   if (eps) {
     if (norm) launch_pass<T, true, false, true, false, true>(nu, a, s, tab, nb);
     else launch_pass<T, true, false, true, false, false>(nu, a, s, tab, nb);
@@ -1006,43 +983,45 @@ template int fused_up<float>(tomg_problem *, int, const float *, float *, const 
 template <typename T>
 static void batch_pass(tomg_problem *const *probs, const int *idx, int cnt, int l, bool up,
                        bool flag, double *const *phis, hipStream_t s) {
-  const bool f32 = std::is_same<T, float>::value;
-  BatchTab tab;
-  for (int k0 = 0; k0 < cnt; k0 += kBatchMax) {
-    tab.count = 0;
-    int nb = 0;
-    const PassArgs<T> *first = nullptr;
-    for (int k = k0; k < cnt && k < k0 + kBatchMax; ++k) {
-      tomg_problem *p = probs[idx[k]];
-      const PassArgs<T> *h = f32 ? (const PassArgs<T> *)(void *)(up ? &p->hargs.up32b[l]
-                                                                      : &p->hargs.down32b[l])
-                                 : (const PassArgs<T> *)(void *)(up ? &p->hargs.up64b[l]
-                                                                      : &p->hargs.down64b[l]);
-      const PassArgs<T> *d = f32 ? (const PassArgs<T> *)(void *)(up ? &p->dargs->up32b[l]
-                                                                      : &p->dargs->down32b[l])
-                                 : (const PassArgs<T> *)(void *)(up ? &p->dargs->up64b[l]
-                                                                      : &p->dargs->down64b[l]);
-      if (!first) first = h;
-      BatchEntry &e = tab.e[tab.count++];
-      e.args = d;
-      e.phi = (!f32 && l == 0) ? (void *)phis[idx[k]] : nullptr;
-      e.role = (!f32 && l == 0) ? (up ? 2 : 1) : 0;
-      e.nbx = h->nbx;
-      e.nby = h->nby;
-      e.start = nb;
-      e.slot = e.out = 0;
-      nb += h->nbx * h->nby;
-    }
-    if (!tab.count) continue;
-    const tomg_problem *p0 = probs[idx[k0]];
-    const int nu = up ? p0->cfg.nu2 : p0->cfg.nu1;
-    // a batch has one level-0 operator form (on-the-fly or stored) for all
-    const bool eps = l == 0 && !stored_level0(p0->cfg);
-    if (up)
-      launch_up<T>(nu, eps, flag, *first, s, &tab, nb);
+  constexpr bool f32 = std::is_same<T, float>::value;
+  auto args = [&](const ArgsBlob &g, bool alone) -> const PassArgs<T> * {
+    if constexpr (f32)
+      return alone ? (up ? &g.up32[l] : &g.down32[l]) : (up ? &g.up32b[l] : &g.down32b[l]);
     else
-      launch_down<T>(nu, eps, flag, *first, s, &tab, nb);
-  }
+      return alone ? (up ? &g.up64[l] : &g.down64[l]) : (up ? &g.up64b[l] : &g.down64b[l]);
+  };
+  BatchTab tab;
+  for (int form = 0; form < kForms; ++form)  // a launch per form
+    for (int k = 0; k < cnt;) {
+      tab.count = 0;
+      int nb = 0;
+      const PassArgs<T> *first = nullptr;
+      for (; k < cnt && tab.count < kBatchMax; ++k) {
+        tomg_problem *p = probs[idx[k]];
+        constexpr bool alone = false;
+        const PassArgs<T> *h = args(p->hargs, alone);
+        if (h->form != form) continue;
+        if (!first) first = h;
+        BatchEntry &e = tab.e[tab.count++];
+        e.args = args(*p->dargs, alone);
+        e.phi = (!f32 && l == 0) ? (void *)phis[idx[k]] : nullptr;
+        e.role = (!f32 && l == 0) ? (up ? 2 : 1) : 0;
+        e.nbx = h->nbx;
+        e.nby = h->nby;
+        e.start = nb;
+        e.slot = e.out = 0;
+        nb += h->nbx * h->nby;
+      }
+      if (!tab.count) continue;
+      const tomg_problem *p0 = probs[idx[0]];
+      const int nu = up ? p0->cfg.nu2 : p0->cfg.nu1;
+      // a batch has one level-0 operator form (on-the-fly or stored) for all
+      const bool eps = l == 0 && !stored_level0(p0->cfg);
+      if (up)
+        launch_up<T>(nu, eps, flag, *first, s, &tab, nb);
+      else
+        launch_down<T>(nu, eps, flag, *first, s, &tab, nb);
+    }
 }
 
 void batch_down(tomg_problem *const *probs, const int *idx, int cnt, int l, bool fp32, bool zero0,

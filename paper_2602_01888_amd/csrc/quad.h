@@ -11,6 +11,8 @@
 
 #include <type_traits>
 
+#include "tomg_internal.h"
+
 namespace tomg {
 
 // ---- arithmetic of one node ---------------------------------------------
@@ -152,6 +154,49 @@ __device__ __forceinline__ T quad_full_weight(const T (&res)[4], const T *cr, in
     col[d] = lo + T(2) * mid + hi;
   }
   return (col[0] + T(2) * col[1] + col[2]) * T(0.0625);
+}
+
+// ---- tiles and bands of a launch -------------------------------------------
+
+// Odd bands march down: then two neighbouring bands reach their common
+// boundary at the same time -- at the start of the pass for one pair, at its
+// end for the other -- and the halo rows both read are served by the cache
+// instead of being fetched from memory twice.  FP64 passes only: the FP32
+// passes move half the bytes and gain nothing from it.
+template <typename T>
+__device__ __forceinline__ bool mirrored(int by, int ny) {
+  return std::is_same<T, double>::value && (by & 1) && (ny & 1);
+}
+
+// Tile of a block of a one-dimensional launch.  Workgroups go to the eight
+// XCDs in turn (XCD = linear id mod 8); each XCD is given one contiguous run
+// of tiles in strip-fastest order, so the neighbouring strips of a band --
+// which read each other's halo columns at about the same time -- share that
+// XCD's L2 instead of fetching the halo twice from memory.
+__device__ __forceinline__ void xcd_tile(int id, int nbx, int nby, int &bx, int &by) {
+  const int n = nbx * nby, per = n >> 3, rem = n & 7;
+  const int xcd = id & 7, q = id >> 3;
+  const int tile = xcd * per + min(xcd, rem) + q;
+  bx = tile % nbx;
+  by = tile / nbx;
+}
+
+// Entry of a batched launch holding block b (entries sorted by start).
+__device__ __forceinline__ const BatchEntry &batch_locate(const BatchTab &tab, int b) {
+  int lo = 0, hi = tab.count - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (tab.e[mid].start <= b) lo = mid; else hi = mid - 1;
+  }
+  return tab.e[lo];
+}
+// Its pass arguments, with the level-0 iterate of this solve.
+template <typename T>
+__device__ __forceinline__ PassArgs<T> batch_args(const BatchEntry &e) {
+  PassArgs<T> a = *static_cast<const PassArgs<T> *>(e.args);
+  if (e.role == 1) a.xin = static_cast<const T *>(e.phi);
+  if (e.role == 2) a.xout = static_cast<T *>(e.phi);
+  return a;
 }
 
 // Two neighbouring elements of a row in one load (rows have no alignment

@@ -198,22 +198,36 @@ __global__ __launch_bounds__(QX *QY) void k_tile(PassArgs<T> a) {
                                                               blockIdx.x / a.nbx);
 }
 
-template <typename T, bool EPS, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
-void launch_shape(const PassArgs<T> &a, hipStream_t s) {
-  const int nb = a.nbx * a.nby;
-  if (a.tile == kTileLarge)
-    hipLaunchKernelGGL((k_tile<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, 32, 16>), nb, 512, 0, s,
-                       a);
+template <typename T, bool EPS, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, int QX,
+          int QY>
+__global__ __launch_bounds__(QX *QY) void k_tile_b(BatchTab tab) {
+  const BatchEntry &e = batch_locate(tab, blockIdx.x);
+  const int local = blockIdx.x - e.start;
+  tile_body<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, QX, QY>(batch_args<T>(e), local % e.nbx,
+                                                              local / e.nbx);
+}
+
+template <typename T, bool EPS, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, int QX,
+          int QY>
+void launch_shape(const PassArgs<T> &a, hipStream_t s, const BatchTab *tab, int nb) {
+  if (tab)
+    hipLaunchKernelGGL((k_tile_b<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, QX, QY>), nb, QX * QY,
+                       0, s, *tab);
   else
-    hipLaunchKernelGGL((k_tile<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, 16, 16>), nb, 256, 0, s,
-                       a);
+    hipLaunchKernelGGL((k_tile<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, QX, QY>), a.nbx * a.nby,
+                       QX * QY, 0, s, a);
 }
 template <typename T, bool EPS, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
-void launch_nu(int nu, const PassArgs<T> &a, hipStream_t s) {
-  if (nu == 1)
-    launch_shape<T, EPS, 1, ZERO, PROLONG, RESTRICT, NORM>(a, s);
+void launch_nu(int nu, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab, int nb) {
+  const bool large = a.form == kFormTileLarge;
+  if (nu == 1 && large)
+    launch_shape<T, EPS, 1, ZERO, PROLONG, RESTRICT, NORM, 32, 16>(a, s, tab, nb);
+  else if (nu == 1)
+    launch_shape<T, EPS, 1, ZERO, PROLONG, RESTRICT, NORM, 16, 16>(a, s, tab, nb);
+  else if (large)
+    launch_shape<T, EPS, 2, ZERO, PROLONG, RESTRICT, NORM, 32, 16>(a, s, tab, nb);
   else
-    launch_shape<T, EPS, 2, ZERO, PROLONG, RESTRICT, NORM>(a, s);
+    launch_shape<T, EPS, 2, ZERO, PROLONG, RESTRICT, NORM, 16, 16>(a, s, tab, nb);
 }
 
 }  // namespace
@@ -225,51 +239,50 @@ void launch_nu(int nu, const PassArgs<T> &a, hipStream_t s) {
 // 257^2 14.7, 16.4 -> 7.9, 6.2; 513^2 21.7, 22.0 -> 15.7, 12.6; 1025^2 39.1,
 // 38.7 -> 36.4, 36.4.  At 2049^2 the two are even (a cycle of a 2049^2
 // problem 295 -> 305 us, FP32 470 -> 464), and the level-0 passes of 4097^2
-// are slower (310 against 240 us a pass).  Up to 257^2 the 32 x 32 tiles
-// give the device enough blocks (513^2 with them: a 513^2 cycle 71.5 -> 77.7
-// us); below, both sizes measure the same.
+// are slower (310 against 240 us a pass).  Small grids take the 32 x 32 tiles,
+// for more blocks; from 257^2 up there are enough of the larger ones, which
+// recompute less halo (a 513^2 cycle 71.5 us with them, 77.7 without).
 constexpr long kTileNodes = 1200000;      // largest level on tiles
-constexpr long kSmallTileNodes = 70000;   // largest level on 32 x 32 tiles
+constexpr long kSmallTileNodes = 20000;   // largest level on 32 x 32 tiles
 template <typename T>
-bool pick_tile(PassArgs<T> &a, int nu, bool res) {
-  a.tile = kTileNone;
+bool pick_tile(PassArgs<T> &a, int nu, bool res, bool batch) {
   const long n = (long)a.nx * a.ny;
-  if (nu > 2 || a.ck != 0 || n > kTileNodes) return false;
-  a.tile = n > kSmallTileNodes ? kTileLarge : kTileSmall;
+  if (nu > 2 || a.ck != 0 || batch || n > kTileNodes) return false;
+  a.form = n > kSmallTileNodes ? kFormTileLarge : kFormTileSmall;
   const int hx = 8 * nu + (res ? 2 : 0), hy = 4 * nu + (res ? 2 : 0);
-  a.W = (a.tile == kTileLarge ? 64 : 32) - hx;
+  a.W = (a.form == kFormTileLarge ? 64 : 32) - hx;
   a.CH = 32 - hy;
   a.nbx = (a.nx + a.W - 1) / a.W;
   a.nby = (a.ny + a.CH - 1) / a.CH;
   a.xcd_order = 0;
   return true;
 }
-template bool pick_tile<double>(PassArgs<double> &, int, bool);
-template bool pick_tile<float>(PassArgs<float> &, int, bool);
+template bool pick_tile<double>(PassArgs<double> &, int, bool, bool);
+template bool pick_tile<float>(PassArgs<float> &, int, bool, bool);
 
 template <typename T>
-void tile_down(int nu, bool eps, bool zero, const PassArgs<T> &a, hipStream_t s) {
+void tile_down(int nu, bool eps, bool zero, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab, int nb) {
   if (eps) {
-    if (zero) launch_nu<T, true, true, false, true, false>(nu, a, s);
-    else launch_nu<T, true, false, false, true, false>(nu, a, s);
+    if (zero) launch_nu<T, true, true, false, true, false>(nu, a, s, tab, nb);
+    else launch_nu<T, true, false, false, true, false>(nu, a, s, tab, nb);
   } else {
-    if (zero) launch_nu<T, false, true, false, true, false>(nu, a, s);
-    else launch_nu<T, false, false, false, true, false>(nu, a, s);
+    if (zero) launch_nu<T, false, true, false, true, false>(nu, a, s, tab, nb);
+    else launch_nu<T, false, false, false, true, false>(nu, a, s, tab, nb);
   }
 }
 template <typename T>
-void tile_up(int nu, bool eps, bool norm, const PassArgs<T> &a, hipStream_t s) {
+void tile_up(int nu, bool eps, bool norm, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab, int nb) {
   if (eps) {
-    if (norm) launch_nu<T, true, false, true, false, true>(nu, a, s);
-    else launch_nu<T, true, false, true, false, false>(nu, a, s);
+    if (norm) launch_nu<T, true, false, true, false, true>(nu, a, s, tab, nb);
+    else launch_nu<T, true, false, true, false, false>(nu, a, s, tab, nb);
   } else {
-    if (norm) launch_nu<T, false, false, true, false, true>(nu, a, s);
-    else launch_nu<T, false, false, true, false, false>(nu, a, s);
+    if (norm) launch_nu<T, false, false, true, false, true>(nu, a, s, tab, nb);
+    else launch_nu<T, false, false, true, false, false>(nu, a, s, tab, nb);
   }
 }
-template void tile_down<double>(int, bool, bool, const PassArgs<double> &, hipStream_t);
-template void tile_down<float>(int, bool, bool, const PassArgs<float> &, hipStream_t);
-template void tile_up<double>(int, bool, bool, const PassArgs<double> &, hipStream_t);
-template void tile_up<float>(int, bool, bool, const PassArgs<float> &, hipStream_t);
+template void tile_down<double>(int, bool, bool, const PassArgs<double> &, hipStream_t, const BatchTab *, int);
+template void tile_down<float>(int, bool, bool, const PassArgs<float> &, hipStream_t, const BatchTab *, int);
+template void tile_up<double>(int, bool, bool, const PassArgs<double> &, hipStream_t, const BatchTab *, int);
+template void tile_up<float>(int, bool, bool, const PassArgs<float> &, hipStream_t, const BatchTab *, int);
 
 }  // namespace tomg

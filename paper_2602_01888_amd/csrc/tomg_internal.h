@@ -64,9 +64,10 @@ struct Level {
 
 // ---- per-problem launch arguments (device copies live in the workspace) ----
 
-// Forms of a level pass: a march up bands (fused.hip), or whole tiles of
-// 64 x 32 or 32 x 32 nodes, halo included (tile.hip).
-enum { kTileNone = 0, kTileSmall = 1, kTileLarge = 2 };
+// Forms of a level pass: bands with the rows in LDS (fused.hip); whole tiles
+// of 32 x 32 or 64 x 32 nodes, halo included (tile.hip); bands with the rows
+// in a wave's registers (march.hip: level 0, operator formed from the tensor).
+enum { kFormBand = 0, kFormTileSmall = 1, kFormTileLarge = 2, kFormMarch = 3, kForms = 4 };
 
 // One fused level pass (fused.hip).
 template <typename T>
@@ -90,7 +91,7 @@ struct PassArgs {
   int xcd_order;             // tiles in XCD-contiguous order (one-dimensional grid)
   int ck;                    // transfer to the coarse level: 0 both axes halved, 1 x, 2 y
   int bw;                    // threads (columns) per block
-  int tile;                  // kTile*: the pass runs on whole tiles of CH x W owned nodes
+  int form;                  // kForm*
   const double *skip;        // nonzero *skip: the launch does nothing (solve()
                              // queues cycles past convergence as no-ops)
 };
@@ -305,14 +306,30 @@ template <typename T>
 void fused_updown(tomg_problem *p, const T *pong, T *out, const T *b, const T *exx,
                   const T *exy, const T *eyy, const T *st, const T *xc, T *bc);
 
-// the same passes on whole tiles (tile.hip): pick_tile sets a's form and
-// blocking (res: the pass forms residuals), the others launch it
+// The other forms of a pass: pick_tile and pick_march give a pass their form
+// and blocking where they are the faster (res: the pass forms residuals),
+// the others launch it (tab, nb: a batched launch and its blocks).
 template <typename T>
-bool pick_tile(PassArgs<T> &a, int nu, bool res);
+bool pick_tile(PassArgs<T> &a, int nu, bool res, bool batch);
 template <typename T>
-void tile_down(int nu, bool eps, bool zero, const PassArgs<T> &a, hipStream_t s);
+void tile_down(int nu, bool eps, bool zero, const PassArgs<T> &a, hipStream_t s,
+               const BatchTab *tab, int nb);
 template <typename T>
-void tile_up(int nu, bool eps, bool norm, const PassArgs<T> &a, hipStream_t s);
+void tile_up(int nu, bool eps, bool norm, const PassArgs<T> &a, hipStream_t s,
+             const BatchTab *tab, int nb);
+template <typename T>
+bool pick_march(PassArgs<T> &a, int nu, bool up, bool batch);
+template <typename T>
+void march_down(int nu, bool zero, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab,
+                int nb);
+template <typename T>
+void march_up(int nu, bool norm, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab,
+              int nb);
+// Rows per block of a band form, alone (slots: blocks resident at once) and
+// in a batch.
+int pick_band(int nx, int ny, int W, long slots, int hv);
+int pick_band_batch(int ny);
+int device_cus();
 
 // levels lc..L-1 of the cycle in one workgroup (tail.hip)
 template <typename T>
