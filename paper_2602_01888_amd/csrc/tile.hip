@@ -242,12 +242,17 @@ void launch_nu(int nu, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab,
 // are slower (310 against 240 us a pass).  Small grids take the 32 x 32 tiles,
 // for more blocks; from 257^2 up there are enough of the larger ones, which
 // recompute less halo (a 513^2 cycle 71.5 us with them, 77.7 without).
+// In a batch that fills the device the marching passes, which recompute less
+// still, are the faster from 257^2 up (256 problems of sides 65 .. 1025, mixed
+// precision: no tiles 23.87 ms, up to 65^2 23.63, 129^2 23.50, 257^2 24.98,
+// 513^2 26.34; FP64 34.10, 33.45, 32.52, 34.00, 34.90).
 constexpr long kTileNodes = 1200000;      // largest level on tiles
 constexpr long kSmallTileNodes = 20000;   // largest level on 32 x 32 tiles
+constexpr long kTileNodesBatch = 20000;   // largest level on tiles in a batch
 template <typename T>
 bool pick_tile(PassArgs<T> &a, int nu, bool res, bool batch) {
   const long n = (long)a.nx * a.ny;
-  if (nu > 2 || a.ck != 0 || batch || n > kTileNodes) return false;
+  if (nu > 2 || a.ck != 0 || n > (batch ? kTileNodesBatch : kTileNodes)) return false;
   a.form = n > kSmallTileNodes ? kFormTileLarge : kFormTileSmall;
   const int hx = 8 * nu + (res ? 2 : 0), hy = 4 * nu + (res ? 2 : 0);
   a.W = (a.form == kFormTileLarge ? 64 : 32) - hx;
