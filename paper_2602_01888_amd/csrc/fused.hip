@@ -540,9 +540,8 @@ __global__ __launch_bounds__(BW, TOMG_MIN_WAVES) void k_pass(PassArgs<T> a) {
 template <typename T, bool EPS, int NU, int P, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM,
           int CK = 0>
 __global__ __launch_bounds__(kBWBatch, TOMG_MIN_WAVES) void k_pass_b(BatchTab tab) {
-  const BatchEntry &e = batch_locate(tab, blockIdx.x);
-  const PassArgs<T> a = batch_args<T>(e);
-  const int local = blockIdx.x - e.start, bx = local % e.nbx, by = local / e.nbx;
+  int bx, by;
+  const PassArgs<T> a = batch_args<T>(tab, bx, by);
   if (mirrored<T>(by, a.ny))
     pass_body<T, EPS, NU, P, ZERO, PROLONG, RESTRICT, NORM, true, CK, kBWBatch>(a, bx, by);
   else

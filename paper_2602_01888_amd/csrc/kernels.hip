@@ -13,6 +13,7 @@
 #include <cstring>
 #include <type_traits>
 
+#include "quad.h"
 #include "tomg_internal.h"
 
 namespace tomg {
@@ -1928,15 +1929,6 @@ __global__ void __launch_bounds__(kRedTileW) k_ir_update(RedArgs a, double *phi,
   ir_update_body(a, phi, xcd_tile_of(blockIdx.x, 0, gridDim.x));
 }
 
-__device__ __forceinline__ const BatchEntry &locate(const BatchTab &tab, int b) {
-  int lo = 0, hi = tab.count - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (tab.e[mid].start <= b) lo = mid; else hi = mid - 1;
-  }
-  return tab.e[lo];
-}
-
 // KIND: a reduction mode (kRm*), -1 for the refinement update alone, or -2
 // for the copy of the iterate from the problem's second array back into the
 // caller's.  With kRmIrStep the iterate moves between the caller's array and
@@ -1945,8 +1937,8 @@ __device__ __forceinline__ const BatchEntry &locate(const BatchTab &tab, int b) 
 // ST: every problem of the launch has a stored level-0 stencil.
 template <int KIND, bool ST>
 __global__ void __launch_bounds__(kRedTileW) k_red_b(BatchTab tab) {
-  const BatchEntry &e = locate(tab, blockIdx.x);
-  const RedArgs &a = *static_cast<const RedArgs *>(e.args);
+  const BatchEntry e = scalar(batch_locate(tab, blockIdx.x));
+  const RedArgs a = scalar(*static_cast<const RedArgs *>(e.args));
   const int t = xcd_tile_of(blockIdx.x, e.start, e.nbx);
   double *phi = static_cast<double *>(e.phi);
   if constexpr (KIND == -2) {

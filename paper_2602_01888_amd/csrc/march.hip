@@ -377,9 +377,8 @@ __global__ __launch_bounds__(64, sizeof(T) == 8 ? 1 : 3) void k_march(PassArgs<T
 }
 template <typename T, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
 __global__ __launch_bounds__(64, sizeof(T) == 8 ? 1 : 3) void k_march_b(BatchTab tab) {
-  const BatchEntry &e = batch_locate(tab, blockIdx.x);
-  const PassArgs<T> a = batch_args<T>(e);
-  const int local = blockIdx.x - e.start, bx = local % e.nbx, by = local / e.nbx;
+  int bx, by;
+  const PassArgs<T> a = batch_args<T>(tab, bx, by);
   if (mirrored<T>(by, a.ny))
     march_body<T, NU, ZERO, PROLONG, RESTRICT, NORM, true>(a, bx, by);
   else

@@ -201,10 +201,9 @@ __global__ __launch_bounds__(QX *QY) void k_tile(PassArgs<T> a) {
 template <typename T, bool EPS, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, int QX,
           int QY>
 __global__ __launch_bounds__(QX *QY) void k_tile_b(BatchTab tab) {
-  const BatchEntry &e = batch_locate(tab, blockIdx.x);
-  const int local = blockIdx.x - e.start;
-  tile_body<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, QX, QY>(batch_args<T>(e), local % e.nbx,
-                                                              local / e.nbx);
+  int bx, by;
+  const PassArgs<T> a = batch_args<T>(tab, bx, by);
+  tile_body<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, QX, QY>(a, bx, by);
 }
 
 template <typename T, bool EPS, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, int QX,
