@@ -601,22 +601,22 @@ size_t fused_max_blocks(int nx, int ny) {
 // level-0 pass that forms its coefficients from the tensor is built).
 template <typename T, bool EPS, int NU, int P, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
 static void launch_small(const PassArgs<T> &a, dim3 grid, hipStream_t s) {
-  if constexpr (!EPS)
+  if constexpr (!EPS && NU > 2)
     hipLaunchKernelGGL((k_pass<T, false, NU, P, ZERO, PROLONG, RESTRICT, NORM, 0, kBWSmall>), grid,
                        dim3(kBWSmall), 0, s, a);
 }
 
-// Both axes halved: with the operator formed from the tensor and at most two
-// sweeps such a pass has another form (pick_march).
+// Both axes halved: with at most two sweeps such a pass has another form
+// (pick_march).
 template <typename T, bool EPS, int NU, int P, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
 static void launch_alone(const PassArgs<T> &a, dim3 grid, hipStream_t s) {
-  if constexpr (!EPS || NU > 2)
+  if constexpr (NU > 2)
     hipLaunchKernelGGL((k_pass<T, EPS, NU, P, ZERO, PROLONG, RESTRICT, NORM>), grid, dim3(kBW), 0,
                        s, a);
 }
 template <typename T, bool EPS, int NU, int P, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
 static void launch_batch(int nblocks, hipStream_t s, const BatchTab &tab) {
-  if constexpr (!EPS || NU > 2)
+  if constexpr (NU > 2)
     hipLaunchKernelGGL((k_pass_b<T, EPS, NU, P, ZERO, PROLONG, RESTRICT, NORM>), dim3(nblocks),
                        dim3(kBWBatch), 0, s, tab);
 }
@@ -674,14 +674,16 @@ int device_cus() {
 template <typename T, bool EPS, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, int BW = kBW>
 static int pass_blocks_per_cu(int nu) {
   constexpr int P = EPS ? TOMG_PAIRS_EPS : TOMG_PAIRS_ST;
-  constexpr int CK = EPS ? 1 : 0;  // up to two sweeps, only semi-coarsened passes have EPS here
+  // up to two sweeps only semi-coarsened passes, on kBW threads, have this form
   const void *f;
-  switch (nu) {
-    case 1: f = reinterpret_cast<const void *>(k_pass<T, EPS, 1, P, ZERO, PROLONG, RESTRICT, NORM, CK, BW>); break;
-    case 2: f = reinterpret_cast<const void *>(k_pass<T, EPS, 2, P, ZERO, PROLONG, RESTRICT, NORM, CK, BW>); break;
-    case 3: f = reinterpret_cast<const void *>(k_pass<T, EPS, 3, P, ZERO, PROLONG, RESTRICT, NORM, 0, BW>); break;
-    default: f = reinterpret_cast<const void *>(k_pass<T, EPS, 4, P, ZERO, PROLONG, RESTRICT, NORM, 0, BW>); break;
-  }
+  if (nu == 3)
+    f = reinterpret_cast<const void *>(k_pass<T, EPS, 3, P, ZERO, PROLONG, RESTRICT, NORM, 0, BW>);
+  else if (nu == 4 || BW != kBW)
+    f = reinterpret_cast<const void *>(k_pass<T, EPS, 4, P, ZERO, PROLONG, RESTRICT, NORM, 0, BW>);
+  else if (nu == 1)
+    f = reinterpret_cast<const void *>(k_pass<T, EPS, 1, P, ZERO, PROLONG, RESTRICT, NORM, 1, kBW>);
+  else
+    f = reinterpret_cast<const void *>(k_pass<T, EPS, 2, P, ZERO, PROLONG, RESTRICT, NORM, 1, kBW>);
   int nb = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, BW, 0) != hipSuccess || nb < 1) nb = 1;
   return nb;
@@ -816,7 +818,7 @@ static PassArgs<T> make_args(tomg_problem *p, int l, bool up, bool batch, T *x0,
   a.ck = v.ck;
   // the residual follows the sweeps in a down pass and where the norm is taken
   if (pick_tile(a, nu, !up || (l == 0 && !f32), batch)) return a;
-  if (l == 0 && !stored && pick_march(a, nu, up, batch)) return a;
+  if (pick_march(a, nu, batch)) return a;
   a.bw = batch ? kBWBatch : (small ? kBWSmall : kBW);
   a.W = a.bw - 2 * (4 * nu + 2);
   a.CH = batch ? pick_band_batch(a.ny)
@@ -872,7 +874,7 @@ void build_pass_args(tomg_problem *p) {
 template <typename T>
 static void launch_down(int nu, bool eps, bool zero, const PassArgs<T> &a, hipStream_t s,
                         const BatchTab *tab, int nb) {
-  if (a.form == kFormMarch) return march_down<T>(nu, zero, a, s, tab, nb);
+  if (a.form == kFormMarch) return march_down<T>(nu, eps, zero, a, s, tab, nb);
   if (a.form != kFormBand) return tile_down<T>(nu, eps, zero, a, s, tab, nb);
   if (eps) {
     if (zero) launch_pass<T, true, true, false, true, false>(nu, a, s, tab, nb);
@@ -886,7 +888,7 @@ static void launch_down(int nu, bool eps, bool zero, const PassArgs<T> &a, hipSt
 template <typename T>
 static void launch_up(int nu, bool eps, bool norm, const PassArgs<T> &a, hipStream_t s,
                       const BatchTab *tab, int nb) {
-  if (a.form == kFormMarch) return march_up<T>(nu, norm, a, s, tab, nb);
+  if (a.form == kFormMarch) return march_up<T>(nu, eps, norm, a, s, tab, nb);
   if (a.form != kFormBand) return tile_up<T>(nu, eps, norm, a, s, tab, nb);
   if (eps) {
     if (norm) launch_pass<T, true, false, true, false, true>(nu, a, s, tab, nb);

@@ -1,6 +1,6 @@
-// Level-0 passes of the large levels, operator formed from the tensor
-// (arXiv 2602.01888, Section 3; eq. 18): one wave marches up a band of rows,
-// two columns per lane.
+// Passes of the large levels (arXiv 2602.01888, Section 3), with the operator
+// formed from the tensor (level 0, eq. 18) or stored: one wave marches up a
+// band of rows, two columns per lane.
 //
 // A lane owns an even and the next odd column, so a step of two rows is one
 // node of each colour per lane (quad.h's order without the quad's LDS): no
@@ -14,6 +14,11 @@
 // (3.4 -> 4.1 TB/s); of a batch of 256 problems of sides 65 .. 1025, FP64 39.1
 // -> 34.1 ms, mixed precision 26.7 -> 23.9 ms.  What is left is the walk
 // itself: a copy of the same bands streams 4.3 .. 4.7 TB/s.
+// With the stencil stored (nine planes: 2049^2 FP64 is 437 MB a pass) the same:
+// the upward pass with its norm 115 -> 96 us, the downward pass 102 -> 97 us
+// (4.5 TB/s), 256 problems of mixed precision 21.1 -> 20.3 ms.  Its six rows of
+// coefficients take 360 .. 446 of a lane's 512 registers at FP64; the diagonal
+// neighbours kept in LDS instead cost a step its LDS reads (107 us).
 //
 // Row order, colours and arithmetic are those of the other passes (fused.hip):
 // at step m sweep s relaxes colours 0 and 1 of row 2m - 2s, then colours 2
@@ -65,34 +70,55 @@ __device__ __forceinline__ T above(T v) {
 // and hold more values than the registers.
 __device__ __forceinline__ void phase() { __builtin_amdgcn_sched_barrier(0); }
 
+// One row as loaded: the lane's two columns.
+template <typename T, bool ST>
+struct Row;
 template <typename T>
-struct Row {  // one row as loaded: the lane's two columns
+struct Row<T, false> {
   T x[2], f[2], xx[2], xy[2], yy[2];
   bool d[2];
 };
 template <typename T>
-struct Coef {  // one row's coefficients
+struct Row<T, true> {
+  T x[2], f[2], a[9][2];
+  bool d[2];
+};
+// One row's coefficients in registers.
+template <typename T, bool ST>
+struct Coef;
+template <typename T>
+struct Coef<T, false> {
   T k1[2], k3[2], k4[2], k5[2], k6[2], ik[2];
   bool on[2];  // the node is relaxed
+};
+template <typename T>
+struct Coef<T, true> {
+  T a[8][2], ik[2];  // S, W, E, N, SW, SE, NW, NE
+  bool on[2];
 };
 // What a lane keeps in LDS for itself (no other lane reads it, so nothing is
 // synchronised): values of the rows in flight that are read only now and
 // then and would not fit the registers beside the rings.
-template <typename T, int NS>
+template <typename T, int NS, bool ST>
 struct Own {
   typedef T V2 __attribute__((ext_vector_type(2)));
   V2 f[NS][64], dg[NS][64];         // right-hand side and diagonal
   V2 xx[64], xy[2][64], yy[2][64];  // tensor of rows 2m-2 (xy, yy) and 2m-1
 };
+template <typename T, int NS>
+struct Own<T, NS, true> {
+  typedef T V2 __attribute__((ext_vector_type(2)));
+  V2 f[NS][64], dg[NS][64];
+};
 
-template <typename T, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, bool MIR>
+template <typename T, bool ST, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, bool MIR>
 __device__ __forceinline__ void march_body(const PassArgs<T> &a, const int bx, const int by) {
   constexpr int HL = 4 * NU + 2;
   // rows 2m+1 .. 2m-2nu are in flight in step m, and the value of the row below
   constexpr int NS = 2 * NU + 2, PER = NS / 2;  // ring slots; steps until they repeat
   typedef typename PairOf<T>::type Pair;
-  __shared__ Own<T, NS> own;
-  typedef typename Own<T, NS>::V2 V2;
+  __shared__ Own<T, NS, ST> own;
+  typedef typename Own<T, NS, ST>::V2 V2;
   const int nx = a.nx, ny = a.ny;
   const int lane = threadIdx.x;
   const int x0 = bx * a.W;
@@ -104,6 +130,8 @@ __device__ __forceinline__ void march_body(const PassArgs<T> &a, const int bx, c
   const bool in0 = i0 >= 0 && i0 < nx, in1 = i0 + 1 >= 0 && i0 + 1 < nx;
   const bool out = lane >= HL / 2 && 2 * lane < HL + a.W && in0;
   const unsigned Ib = (unsigned)min(max(i0 >> 1, 0), a.nxc - 2);
+  const size_t n = (size_t)nx * ny;
+  (void)n;
   // MIR: the block marches down its band in flipped row coordinates (row r
   // is grid row ny-1-r; ny is odd, so parities and colours stay) and sums in
   // the order of the upward march
@@ -112,14 +140,16 @@ __device__ __forceinline__ void march_body(const PassArgs<T> &a, const int bx, c
   const int ys = max(0, (y0 - (2 * NU + 1)) & ~1);
   const int ye = min(ny - 1, ((y1 - 1) | 1) + 2 * NU);
   // rows relaxed: those with both neighbours loaded, and the grid's edges
-  // (Dirichlet rows: nothing there is relaxed)
+  // (Dirichlet, or free rows whose outer coefficients are zero)
   const int rlo = ys == 0 ? 0 : ys + 1, rn = (ye == ny - 1 ? ye : ye - 1) - rlo;
   const int m0 = ys >> 1;
 
+  auto row_on = [&](int r) { return (unsigned)(r - rlo) <= (unsigned)rn; };
+
   // Nodes outside the grid hold whatever their clamped loads gave: none is
-  // relaxed, and only Dirichlet nodes, which are not relaxed either, have
-  // such neighbours.
-  auto load_row = [&](int r, Row<T> &w) {
+  // relaxed, and only nodes of the grid's edge have such neighbours, which
+  // are not relaxed either (Dirichlet) or have zero coefficients there.
+  auto load_row = [&](int r, Row<T, ST> &w) {
     const int rc = min(r, ny - 1);
     const size_t at = (size_t)(MIR ? ny - 1 - rc : rc) * nx;
     auto get = [&](const T *p, T(&v)[2]) {
@@ -129,31 +159,42 @@ __device__ __forceinline__ void march_body(const PassArgs<T> &a, const int bx, c
     };
     if constexpr (!ZERO) get(a.xin, w.x);
     get(a.b, w.f);
-    get(a.exx, w.xx);
-    get(a.exy, w.xy);
-    get(a.eyy, w.yy);
+    if constexpr (ST) {
+#pragma unroll
+      for (int z = 0; z < 9; ++z) get(a.st + z * n, w.a[z]);
+    } else {
+      get(a.exx, w.xx);
+      get(a.exy, w.xy);
+      get(a.eyy, w.yy);
+    }
     const uint8_t *d = a.dir + at + ib;
     w.d[0] = d[0] != 0;
     w.d[1] = d[1] != 0;
   };
-  auto fix_last = [&](Row<T> &w) {
+  auto fix_last = [&](Row<T, ST> &w) {
     if (!edge) return;
     if constexpr (!ZERO) w.x[0] = last ? w.x[1] : w.x[0];
     w.f[0] = last ? w.f[1] : w.f[0];
-    w.xx[0] = last ? w.xx[1] : w.xx[0];
-    w.xy[0] = last ? w.xy[1] : w.xy[0];
-    w.yy[0] = last ? w.yy[1] : w.yy[0];
+    if constexpr (ST) {
+#pragma unroll
+      for (int z = 0; z < 9; ++z) w.a[z][0] = last ? w.a[z][1] : w.a[z][0];
+    } else {
+      w.xx[0] = last ? w.xx[1] : w.xx[0];
+      w.xy[0] = last ? w.xy[1] : w.xy[0];
+      w.yy[0] = last ? w.yy[1] : w.yy[0];
+    }
     w.d[0] = last ? w.d[1] : w.d[0];
   };
   auto load_coarse = [&](int J, T (&v)[2]) {  // coarse row J (flipped with the rows)
     const int j = min(J, a.nyc - 1);
     const Pair q = load_pair(a.xc + (size_t)(MIR ? a.nyc - 1 - j : j) * a.nxc + Ib);
-    v[0] = q[0];  // (column nx-1 is Dirichlet: its lane's pair is not used)
+    // (column nx-1 is Dirichlet without a stored stencil: its pair is not used)
+    v[0] = ST && last ? q[1] : q[0];
     v[1] = q[1];
   };
   // value of a loaded row, with the correction of the coarse rows under row
   // r & ~1 (lo) and above it (hi)
-  auto commit = [&](int q, const Row<T> &w, const T (&lo)[2], const T (&hi)[2], T (&v)[2]) {
+  auto commit = [&](int q, const Row<T, ST> &w, const T (&lo)[2], const T (&hi)[2], T (&v)[2]) {
     v[0] = ZERO ? T(0) : w.x[0];
     v[1] = ZERO ? T(0) : w.x[1];
     if constexpr (PROLONG) {
@@ -168,24 +209,47 @@ __device__ __forceinline__ void march_body(const PassArgs<T> &a, const int bx, c
   };
 
   T V[NS][2], vb[2] = {T(0), T(0)};  // vb: row 2m-2nu-1
-  Coef<T> C[NS];
+  Coef<T, ST> C[NS];
   auto slot = [](int rel) { return ((rel % NS) + NS) % NS; };
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       V[s][k] = T(0);
-      C[s].k1[k] = C[s].k3[k] = C[s].k4[k] = C[s].k5[k] = C[s].k6[k] = C[s].ik[k] = T(0);
+      if constexpr (ST) {
+#pragma unroll
+        for (int z = 0; z < 8; ++z) C[s].a[z][k] = T(0);
+      } else {
+        C[s].k1[k] = C[s].k3[k] = C[s].k4[k] = C[s].k5[k] = C[s].k6[k] = T(0);
+      }
+      C[s].ik[k] = T(0);
       C[s].on[k] = false;
     }
     own.f[s][lane] = own.dg[s][lane] = V2{T(0), T(0)};
   }
-  own.xx[lane] = own.xy[0][lane] = own.xy[1][lane] = own.yy[0][lane] = own.yy[1][lane] =
-      V2{T(0), T(0)};
+  if constexpr (!ST)
+    own.xx[lane] = own.xy[0][lane] = own.xy[1][lane] = own.yy[0][lane] = own.yy[1][lane] =
+        V2{T(0), T(0)};
+  // a loaded row r into its ring slot s: right-hand side and, when stored, the stencil
+  auto enter = [&](int r, int s, const Row<T, ST> &w) {
+    own.f[s][lane] = V2{w.f[0], w.f[1]};
+    if constexpr (ST) {
+      constexpr int kOrder[8] = {1, 3, 5, 7, 0, 2, 6, 8};
+      const bool ok = row_on(r);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+#pragma unroll
+        for (int z = 0; z < 8; ++z) C[s].a[z][k] = w.a[kOrder[z]][k];
+        C[s].ik[k] = T(1) / w.a[4][k];
+        C[s].on[k] = ok && !w.d[k] && (k ? in1 : in0);
+      }
+      own.dg[s][lane] = V2{w.a[4][0], w.a[4][1]};
+    }
+  };
   bool pd0 = true, pd1 = true;  // Dirichlet flags of row 2m-1
   T rprev[2] = {T(0), T(0)};
   double acc = 0.0;
-  Row<T> cur[2], nxt[2];
+  Row<T, ST> cur[2], nxt[2];
   T c0[2] = {T(0), T(0)}, c1[2] = {T(0), T(0)}, c2[2] = {T(0), T(0)};  // coarse rows m .. m+2
   load_row(2 * m0, cur[0]);
   load_row(2 * m0 + 1, cur[1]);
@@ -197,7 +261,7 @@ __device__ __forceinline__ void march_body(const PassArgs<T> &a, const int bx, c
   for (int q = 0; q < 2; ++q) {
     fix_last(cur[q]);
     commit(q, cur[q], c0, c1, V[slot(q)]);
-    own.f[slot(q)][lane] = V2{cur[q].f[0], cur[q].f[1]};
+    enter(2 * m0 + q, slot(q), cur[q]);
   }
 
   for (int sb = 0;; sb += PER) {
@@ -208,14 +272,13 @@ __device__ __forceinline__ void march_body(const PassArgs<T> &a, const int bx, c
       if (R0 > y1 - 1) goto done;
       {
         const int rel0 = 2 * ph;  // ring position of row 2m
-        // coefficients of rows 2m-1 (v = 0) and 2m (v = 1)
-        {
+        if constexpr (!ST) {  // coefficients of rows 2m-1 (v = 0) and 2m (v = 1)
           const V2 pxx = own.xx[lane], pxy = own.xy[1][lane], pyy = own.yy[1][lane];
           const V2 qxy = own.xy[0][lane], qyy = own.yy[0][lane];
 #pragma unroll
           for (int v = 0; v < 2; ++v) {
-            Coef<T> &c = C[slot(rel0 - 1 + v)];
-            const bool rowok = (unsigned)(2 * m - 1 + v - rlo) <= (unsigned)rn;
+            Coef<T, ST> &c = C[slot(rel0 - 1 + v)];
+            const bool rowok = row_on(2 * m - 1 + v);
             const T xx[2] = {v ? cur[0].xx[0] : pxx[0], v ? cur[0].xx[1] : pxx[1]};
             const T xy[2] = {v ? cur[0].xy[0] : pxy[0], v ? cur[0].xy[1] : pxy[1]};
             const T yy[2] = {v ? cur[0].yy[0] : pyy[0], v ? cur[0].yy[1] : pyy[1]};
@@ -255,19 +318,25 @@ __device__ __forceinline__ void march_body(const PassArgs<T> &a, const int bx, c
         load_row(2 * m + 3, nxt[1]);
         if constexpr (PROLONG) load_coarse(m + 2, c2);
         phase();
-        // f minus the off-centre part at column k of row 2m + o
+        // f minus the off-centre part of node (row 2m + o, column k)
         auto node_defect = [&](int o, int k, T f) -> T {
-          const Coef<T> &c = C[slot(rel0 + o)];
+          const Coef<T, ST> &c = C[slot(rel0 + o)];
           const T(&mid)[2] = V[slot(rel0 + o)];
           const T(&dn)[2] = o == -2 * NU ? vb : V[slot(rel0 + o - 1)];
           const T(&up)[2] = V[slot(rel0 + o + 1)];
           const T(&lo)[2] = MIR ? up : dn;
           const T(&hi)[2] = MIR ? dn : up;
-          if (k == 0)
-            return defect18(f, c.k1[0], c.k3[0], c.k4[0], c.k5[0], c.k6[0], below(lo[1]), lo[0],
-                            lo[1], below(mid[1]), mid[1], below(hi[1]), hi[0], hi[1]);
-          return defect18(f, c.k1[1], c.k3[1], c.k4[1], c.k5[1], c.k6[1], lo[0], lo[1],
-                          above(lo[0]), mid[0], above(mid[0]), hi[0], hi[1], above(hi[0]));
+          const T sw = k ? lo[0] : below(lo[1]), se = k ? above(lo[0]) : lo[1];
+          const T ww = k ? mid[0] : below(mid[1]), ee = k ? above(mid[0]) : mid[1];
+          const T nw = k ? hi[0] : below(hi[1]), ne = k ? above(hi[0]) : hi[1];
+          if constexpr (ST) {
+            const T a9[9] = {c.a[4][k], c.a[0][k], c.a[5][k], c.a[1][k], T(0),
+                             c.a[2][k], c.a[6][k], c.a[3][k], c.a[7][k]};
+            return defect9(f, a9, sw, lo[k], se, ww, ee, nw, hi[k], ne);
+          } else {
+            return defect18(f, c.k1[k], c.k3[k], c.k4[k], c.k5[k], c.k6[k], sw, lo[k], se, ww,
+                            ee, nw, hi[k], ne);
+          }
         };
 #pragma unroll
         for (int s = 0; s < NU; ++s)
@@ -277,7 +346,7 @@ __device__ __forceinline__ void march_body(const PassArgs<T> &a, const int bx, c
             const V2 f = own.f[slot(rel0 + o)][lane];
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
-              const Coef<T> &c = C[slot(rel0 + o)];
+              const Coef<T, ST> &c = C[slot(rel0 + o)];
               const T v = relaxed(node_defect(o, k, f[k]), c.ik[k]);
               T &x = V[slot(rel0 + o)][k];
               x = c.on[k] ? v : x;
@@ -292,7 +361,7 @@ __device__ __forceinline__ void march_body(const PassArgs<T> &a, const int bx, c
           const T(&mid)[2] = V[slot(rel0 + o)];
           const bool band = (unsigned)(r - y0) < (unsigned)(y1 - y0);
           if constexpr (RESTRICT || NORM) {
-            const Coef<T> &c = C[slot(rel0 + o)];
+            const Coef<T, ST> &c = C[slot(rel0 + o)];
             const V2 f = own.f[slot(rel0 + o)][lane], dg = own.dg[slot(rel0 + o)][lane];
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
@@ -328,10 +397,11 @@ __device__ __forceinline__ void march_body(const PassArgs<T> &a, const int bx, c
           const int J = R0 >> 1;
           if ((unsigned)(R0 - y0) < (unsigned)(y1 - y0) && out) {
             const int I = i0 >> 1, Jg = MIR ? a.nyc - 1 - J : J;
-            // the coarse ring is Dirichlet
-            const bool ring = I == 0 || Jg == 0 || I == a.nxc - 1 || Jg == a.nyc - 1;
+            // a coarse ring node is Dirichlet unless its edge is Neumann
+            bool fixed = I == 0 || Jg == 0 || I == a.nxc - 1 || Jg == a.nyc - 1;
+            if constexpr (ST) fixed = fixed && (!a.dirc || a.dirc[(size_t)Jg * a.nxc + I]);
             const T v = (w + T(2) * s[0] + s[1]) * T(0.0625);
-            __builtin_nontemporal_store(ring ? T(0) : v, a.bc + (size_t)Jg * a.nxc + (unsigned)I);
+            __builtin_nontemporal_store(fixed ? T(0) : v, a.bc + (size_t)Jg * a.nxc + (unsigned)I);
           }
         }
         phase();
@@ -347,8 +417,8 @@ __device__ __forceinline__ void march_body(const PassArgs<T> &a, const int bx, c
         for (int q = 0; q < 2; ++q) {
           fix_last(nxt[q]);
           commit(q, nxt[q], c0, c1, V[slot(rel0 + 2 + q)]);
-          own.f[slot(rel0 + 2 + q)][lane] = V2{nxt[q].f[0], nxt[q].f[1]};
-          cur[q] = nxt[q];
+          enter(2 * m + 2 + q, slot(rel0 + 2 + q), nxt[q]);
+          if constexpr (!ST) cur[q] = nxt[q];
         }
       }
     }
@@ -361,64 +431,57 @@ done:
   }
 }
 
-// One wave of FP64 per SIMD, three of FP32: what the registers in flight
-// allow (FP64 256 VGPRs and 20 .. 30 of the accumulation file; FP32 140 .. 150).
-// Held to two waves, FP64 spills to scratch: a 4097^2 cycle 825 against 752
-// us; FP32 at four 1408 against 1131 us (a refinement step of two cycles).
-template <typename T, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
-__global__ __launch_bounds__(64, sizeof(T) == 8 ? 1 : 3) void k_march(PassArgs<T> a) {
+// Waves per SIMD: what the registers in flight allow.  From the tensor FP64
+// takes 256 VGPRs and 20 .. 30 of the accumulation file, FP32 140 .. 150; held
+// to two waves FP64 spills to scratch (a 4097^2 cycle 825 against 752 us), as
+// does FP32 at four (two cycles and their refinement step 1408 against 1131
+// us).  The stored rows take 512 and 256 registers: one wave and two.
+template <typename T, bool ST>
+constexpr int march_waves() {
+  return sizeof(T) == 8 ? 1 : (ST ? 2 : 3);
+}
+template <typename T, bool ST, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
+__global__ __launch_bounds__(64, (march_waves<T, ST>())) void k_march(PassArgs<T> a) {
   if (a.skip && *a.skip != 0.0) return;
   int bx = blockIdx.x, by = blockIdx.y;
   if (a.xcd_order) xcd_tile(blockIdx.x, a.nbx, a.nby, bx, by);
   if (mirrored<T>(by, a.ny))
-    march_body<T, NU, ZERO, PROLONG, RESTRICT, NORM, true>(a, bx, by);
+    march_body<T, ST, NU, ZERO, PROLONG, RESTRICT, NORM, true>(a, bx, by);
   else
-    march_body<T, NU, ZERO, PROLONG, RESTRICT, NORM, false>(a, bx, by);
+    march_body<T, ST, NU, ZERO, PROLONG, RESTRICT, NORM, false>(a, bx, by);
 }
-template <typename T, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
-__global__ __launch_bounds__(64, sizeof(T) == 8 ? 1 : 3) void k_march_b(BatchTab tab) {
+template <typename T, bool ST, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
+__global__ __launch_bounds__(64, (march_waves<T, ST>())) void k_march_b(BatchTab tab) {
   int bx, by;
   const PassArgs<T> a = batch_args<T>(tab, bx, by);
   if (mirrored<T>(by, a.ny))
-    march_body<T, NU, ZERO, PROLONG, RESTRICT, NORM, true>(a, bx, by);
+    march_body<T, ST, NU, ZERO, PROLONG, RESTRICT, NORM, true>(a, bx, by);
   else
-    march_body<T, NU, ZERO, PROLONG, RESTRICT, NORM, false>(a, bx, by);
+    march_body<T, ST, NU, ZERO, PROLONG, RESTRICT, NORM, false>(a, bx, by);
 }
 
-template <typename T, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
+template <typename T, bool ST, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
 void launch(const PassArgs<T> &a, hipStream_t s, const BatchTab *tab, int nb) {
   if (tab)
-    hipLaunchKernelGGL((k_march_b<T, NU, ZERO, PROLONG, RESTRICT, NORM>), nb, 64, 0, s, *tab);
+    hipLaunchKernelGGL((k_march_b<T, ST, NU, ZERO, PROLONG, RESTRICT, NORM>), nb, 64, 0, s, *tab);
   else
-    hipLaunchKernelGGL((k_march<T, NU, ZERO, PROLONG, RESTRICT, NORM>),
+    hipLaunchKernelGGL((k_march<T, ST, NU, ZERO, PROLONG, RESTRICT, NORM>),
                        a.xcd_order ? dim3(a.nbx * a.nby) : dim3(a.nbx, a.nby), 64, 0, s, a);
 }
-template <typename T, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
+template <typename T, bool ST, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
 void launch_nu(int nu, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab, int nb) {
   if (nu == 1)
-    launch<T, 1, ZERO, PROLONG, RESTRICT, NORM>(a, s, tab, nb);
+    launch<T, ST, 1, ZERO, PROLONG, RESTRICT, NORM>(a, s, tab, nb);
   else
-    launch<T, 2, ZERO, PROLONG, RESTRICT, NORM>(a, s, tab, nb);
-}
-
-// Blocks of a pass that fit on a CU at once.
-template <typename T, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
-int blocks_per_cu(int nu) {
-  const void *f = nu == 1
-                      ? reinterpret_cast<const void *>(k_march<T, 1, ZERO, PROLONG, RESTRICT, NORM>)
-                      : reinterpret_cast<const void *>(k_march<T, 2, ZERO, PROLONG, RESTRICT, NORM>);
-  int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, 64, 0) != hipSuccess || nb < 1) nb = 1;
-  return nb;
+    launch<T, ST, 2, ZERO, PROLONG, RESTRICT, NORM>(a, s, tab, nb);
 }
 
 }  // namespace
 
-// Gives a level-0 pass (operator formed from the tensor) the marching form:
-// both axes halved, at most two sweeps (three sweeps' rows do not fit the
-// registers).
+// Gives a pass the marching form: both axes halved, at most two sweeps (three
+// sweeps' rows do not fit the registers).
 template <typename T>
-bool pick_march(PassArgs<T> &a, int nu, bool up, bool batch) {
+bool pick_march(PassArgs<T> &a, int nu, bool batch) {
   if (nu > 2 || a.ck != 0) return false;
   a.form = kFormMarch;
   a.bw = 64;
@@ -426,39 +489,50 @@ bool pick_march(PassArgs<T> &a, int nu, bool up, bool batch) {
   if (batch) {
     a.CH = pick_band_batch(a.ny);
   } else {
-    constexpr bool F64 = std::is_same<T, double>::value;
-    const int nb = up ? blocks_per_cu<T, false, true, false, F64>(nu)
-                      : blocks_per_cu<T, !F64, false, true, false>(nu);
+    // As many one-wave blocks as the four SIMDs of every CU hold: half of them
+    // on twice as tall bands, with fewer halo rows, leave SIMDs idle (stored
+    // 2049^2 FP64 112 / 100 against 97 / 96 us, a 4097^2 cycle 760 against 741).
     static const int cus = device_cus();
-    a.CH = pick_band(a.nx, a.ny, a.W, (long)nb * cus, 2 * nu + 3);
+    const int waves = 4 * (a.st ? march_waves<T, true>() : march_waves<T, false>());
+    a.CH = pick_band(a.nx, a.ny, a.W, (long)waves * cus, 2 * nu + 3);
   }
   a.nbx = (a.nx + a.W - 1) / a.W;
   a.nby = (a.ny + a.CH - 1) / a.CH;
   a.xcd_order = !batch && a.nbx > 1 ? 1 : 0;
   return true;
 }
-template bool pick_march<double>(PassArgs<double> &, int, bool, bool);
-template bool pick_march<float>(PassArgs<float> &, int, bool, bool);
+template bool pick_march<double>(PassArgs<double> &, int, bool);
+template bool pick_march<float>(PassArgs<float> &, int, bool);
 
 template <typename T>
-void march_down(int nu, bool zero, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab,
-                int nb) {
-  if (zero) launch_nu<T, true, false, true, false>(nu, a, s, tab, nb);
-  else launch_nu<T, false, false, true, false>(nu, a, s, tab, nb);
+void march_down(int nu, bool eps, bool zero, const PassArgs<T> &a, hipStream_t s,
+                const BatchTab *tab, int nb) {
+  if (eps) {
+    if (zero) launch_nu<T, false, true, false, true, false>(nu, a, s, tab, nb);
+    else launch_nu<T, false, false, false, true, false>(nu, a, s, tab, nb);
+  } else {
+    if (zero) launch_nu<T, true, true, false, true, false>(nu, a, s, tab, nb);
+    else launch_nu<T, true, false, false, true, false>(nu, a, s, tab, nb);
+  }
 }
 template <typename T>
-void march_up(int nu, bool norm, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab,
-              int nb) {
-  if (norm) launch_nu<T, false, true, false, true>(nu, a, s, tab, nb);
-  else launch_nu<T, false, true, false, false>(nu, a, s, tab, nb);
+void march_up(int nu, bool eps, bool norm, const PassArgs<T> &a, hipStream_t s,
+              const BatchTab *tab, int nb) {
+  if (eps) {
+    if (norm) launch_nu<T, false, false, true, false, true>(nu, a, s, tab, nb);
+    else launch_nu<T, false, false, true, false, false>(nu, a, s, tab, nb);
+  } else {
+    if (norm) launch_nu<T, true, false, true, false, true>(nu, a, s, tab, nb);
+    else launch_nu<T, true, false, true, false, false>(nu, a, s, tab, nb);
+  }
 }
-template void march_down<double>(int, bool, const PassArgs<double> &, hipStream_t,
-                                  const BatchTab *, int);
-template void march_down<float>(int, bool, const PassArgs<float> &, hipStream_t,
-                                  const BatchTab *, int);
-template void march_up<double>(int, bool, const PassArgs<double> &, hipStream_t,
-                                  const BatchTab *, int);
-template void march_up<float>(int, bool, const PassArgs<float> &, hipStream_t,
-                                  const BatchTab *, int);
+template void march_down<double>(int, bool, bool, const PassArgs<double> &, hipStream_t,
+                                 const BatchTab *, int);
+template void march_down<float>(int, bool, bool, const PassArgs<float> &, hipStream_t,
+                                const BatchTab *, int);
+template void march_up<double>(int, bool, bool, const PassArgs<double> &, hipStream_t,
+                               const BatchTab *, int);
+template void march_up<float>(int, bool, bool, const PassArgs<float> &, hipStream_t,
+                              const BatchTab *, int);
 
 }  // namespace tomg

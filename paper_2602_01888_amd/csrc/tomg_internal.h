@@ -64,9 +64,9 @@ struct Level {
 
 // ---- per-problem launch arguments (device copies live in the workspace) ----
 
-// Forms of a level pass: bands with the rows in LDS (fused.hip); whole tiles
-// of 32 x 32 or 64 x 32 nodes, halo included (tile.hip); bands with the rows
-// in a wave's registers (march.hip: level 0, operator formed from the tensor).
+// Forms of a level pass: bands with the rows in LDS (fused.hip: any sweep
+// count and transfer); whole tiles of 32 x 32 or 64 x 32 nodes, halo included
+// (tile.hip); bands with the rows in a wave's registers (march.hip).
 enum { kFormBand = 0, kFormTileSmall = 1, kFormTileLarge = 2, kFormMarch = 3, kForms = 4 };
 
 // One fused level pass (fused.hip).
@@ -318,13 +318,13 @@ template <typename T>
 void tile_up(int nu, bool eps, bool norm, const PassArgs<T> &a, hipStream_t s,
              const BatchTab *tab, int nb);
 template <typename T>
-bool pick_march(PassArgs<T> &a, int nu, bool up, bool batch);
+bool pick_march(PassArgs<T> &a, int nu, bool batch);
 template <typename T>
-void march_down(int nu, bool zero, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab,
-                int nb);
+void march_down(int nu, bool eps, bool zero, const PassArgs<T> &a, hipStream_t s,
+                const BatchTab *tab, int nb);
 template <typename T>
-void march_up(int nu, bool norm, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab,
-              int nb);
+void march_up(int nu, bool eps, bool norm, const PassArgs<T> &a, hipStream_t s,
+              const BatchTab *tab, int nb);
 // Rows per block of a band form, alone (slots: blocks resident at once) and
 // in a batch.
 int pick_band(int nx, int ny, int W, long slots, int hv);
