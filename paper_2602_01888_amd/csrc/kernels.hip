@@ -1107,113 +1107,172 @@ __global__ void k_rediscretize(const double *__restrict__ exx, const double *__r
 
 constexpr int kInvThreads = 1024, kInvWaves = kInvThreads / 64;
 
+// Lane l's value of a double (l uniform).
+__device__ __forceinline__ double lane_value(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// A uniform value held per lane: what is selected by it takes no branch.
+__device__ __forceinline__ int per_lane(int v) {
+  asm("" : "+v"(v));
+  return v;
+}
+
+constexpr int kGjWaves = 8, kGjThreads = 64 * kGjWaves;
+static_assert(kMaxCoarseUnknowns <= 64 && kSmallCoarseNodes <= 128,
+              "one lane per column, two lanes' worth of nodes");
+
+// A wave's pivot candidate: magnitude, row, wave.
+struct alignas(16) PivotCand {
+  double v;
+  int p, w;
+};
+template <int PERM>
+__device__ __forceinline__ void better_of_two(PivotCand &a) {
+  PivotCand b;
+  b.v = __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(a.v), PERM, 0xf, 0xf, true),
+                         __builtin_amdgcn_update_dpp(0, __double2loint(a.v), PERM, 0xf, 0xf, true));
+  b.p = __builtin_amdgcn_update_dpp(0, a.p, PERM, 0xf, 0xf, true);
+  b.w = __builtin_amdgcn_update_dpp(0, a.w, PERM, 0xf, 0xf, true);
+  const bool take = (b.v > a.v) | ((b.v == a.v) & (b.p < a.p));
+  a.v = take ? b.v : a.v;
+  a.p = take ? b.p : a.p;
+  a.w = take ? b.w : a.w;
+}
+
 // Coarsest level: index map of the free nodes and the explicit inverse of
 // the coarsest matrix by Gauss-Jordan elimination with partial pivoting (one
 // block).  cidx[ncoarse] receives the unknown count.
+//
+// The elimination is a chain of m steps, so its time is a step's latency.
+// It works in place: before step k column c < k of the matrix, a unit vector,
+// gives its place to the column of the inverse that its pivot row started
+// with.  Lane t & 63 owns a column, wave t >> 6 every kGjWaves-th row, in
+// registers: a step's multipliers are lane k's values of the own rows.  Every
+// wave publishes its best pivot candidate with the whole row (and row k's
+// owner that row) in LDS, and after the step's one barrier each picks the
+// winner and updates its rows; two buffers, so that the next step's
+// candidates need no second barrier.  49 unknowns 78 -> 60 us, 21 unknowns 32
+// -> 28 us, from matrix and inverse side by side in LDS with a search by one
+// wave and three barriers a step.  Four waves of twice the rows 65 us, sixteen
+// 74 us: what a step does per wave, not per row, is half of it.
 __device__ __forceinline__ void coarse_inverse_body(const double *st, const uint8_t *dir, int nx,
                                                     int ny, double *inv, int *cidx,
                                                     double *scal) {
-  // Gauss-Jordan with partial pivoting on m <= kMaxCoarseUnknowns < 64
-  // unknowns: lane t & 63 owns a column, wave t >> 6 every kInvWaves-th row
-  // (sixteen waves: three or four rows each on 49 unknowns, so the
-  // elimination of a pivot step is short next to its barriers); the pivot
-  // search is a shuffle reduction in wave 0
-  constexpr int M = kMaxCoarseUnknowns;
-  __shared__ double A[M][M + 1], B[M][M + 1];
-  __shared__ double fac[M], rowa[M], rowb[M];
-  __shared__ int cid[81];
-  __shared__ int sm;
-  const int n = nx * ny, t = threadIdx.x, c = t & 63, w = t >> 6;
-  if (t == 0) {
-    int m = 0;
-    for (int q = 0; q < n; ++q) cid[q] = dir[q] ? -1 : m++;
-    sm = m;
-    for (int q = 0; q < n; ++q) cidx[q] = cid[q];
-    cidx[n] = m;
-  }
-  __syncthreads();
-  const int m = sm;
-  if (c < m)
-    for (int r = w; r < m; r += kInvWaves) {
-      A[r][c] = 0.0;
-      B[r][c] = (r == c) ? 1.0 : 0.0;
+  constexpr int R = (kMaxCoarseUnknowns + kGjWaves - 1) / kGjWaves;
+  __shared__ double row[2][kGjWaves + 1][64];  // candidate rows, then row k
+  __shared__ PivotCand cand[2][kGjWaves];
+  __shared__ int node[64], col[64], lvl[64];  // an unknown's node and its grid indices
+  const int n = nx * ny, t = threadIdx.x, c = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  // free nodes numbered in order: the bits below a node's own
+  const unsigned long long f0 = __ballot(c < n && !dir[min(c, n - 1)]);
+  const unsigned long long f1 = __ballot(c + 64 < n && !dir[min(c + 64, n - 1)]);
+  const int m0 = __popcll(f0), m = m0 + __popcll(f1);
+  if (w < 2) {
+    const unsigned long long f = w ? f1 : f0;
+    const int q = c + 64 * w;
+    const int id = (f >> c) & 1 ? (w ? m0 : 0) + __popcll(f & ((1ull << c) - 1)) : -1;
+    if (q < n) cidx[q] = id;
+    if (id >= 0) {
+      node[id] = q;
+      col[id] = q % nx;
+      lvl[id] = q / nx;
     }
-  __syncthreads();
-  for (int q = t; q < n; q += kInvThreads) {
-    const int row = cid[q];
-    if (row < 0) continue;
-    const int I = q % nx, J = q / nx;
-    for (int dj = -1; dj <= 1; ++dj)
-      for (int di = -1; di <= 1; ++di) {
-        const int ii = I + di, jj = J + dj;
-        if (ii < 0 || jj < 0 || ii >= nx || jj >= ny) continue;
-        const int col = cid[jj * nx + ii];
-        if (col >= 0) A[row][col] = st[(size_t)((dj + 1) * 3 + di + 1) * n + q];
-      }
+    if (t == 0) cidx[n] = m;
   }
   __syncthreads();
-  // scale of the pivot test: the largest diagonal magnitude (wave 0, lanes
-  // over rows); a pivot below 1e-12 of it marks the matrix singular (a
-  // problem without Dirichlet nodes, for example: its operator annihilates
-  // constants on every level)
-  __shared__ double dscale;
-  if (w == 0) {
-    double d = c < m ? fabs(A[c][c]) : 0.0;
+  double A[R];
+  const bool in = c < m;
+  const int qc = in ? node[c] : 0, Ic = in ? col[c] : 0, Jc = in ? lvl[c] : 0;
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) d = fmax(d, __shfl_xor(d, off, 64));
-    if (c == 0) {
-      dscale = d;
-      scal[kSlotPivot] = 0.0;  // this setup's own verdict
-    }
+  for (int i = 0; i < R; ++i) {
+    const int r = w + i * kGjWaves, rc = min(r, max(m - 1, 0));
+    const int di = m ? Ic - col[rc] : 2, dj = m ? Jc - lvl[rc] : 2;
+    const bool near = in & (r < m) & (di >= -1) & (di <= 1) & (dj >= -1) & (dj <= 1);
+    const double x = st[near ? ((dj + 1) * 3 + di + 1) * n + node[rc] : 0];
+    A[i] = near ? x : 0.0;
   }
-  __syncthreads();
-  const double tiny = 1e-12 * dscale;
+  // scale of the pivot test: the largest diagonal magnitude; a pivot below
+  // 1e-12 of it marks the matrix singular (a problem without Dirichlet nodes,
+  // for example: its operator annihilates constants on every level)
+  double tiny = in ? fabs(st[(size_t)4 * n + qc]) : 0.0;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) tiny = fmax(tiny, __shfl_xor(tiny, off, 64));
+  tiny *= 1e-12;
+  if (t == 0) scal[kSlotPivot] = 0.0;  // this setup's own verdict
+  int from = c;  // the row that position c held at the start
+#pragma unroll 1
   for (int k = 0; k < m; ++k) {
-    if (w == 0) {
-      // largest |A[r][k]| for r >= k, the first on ties
-      double v = (c >= k && c < m) ? fabs(A[c][k]) : -1.0;
-      int p = c;
+    const int h = k & 1, kl = per_lane(k);
+    // largest |A[r][c]| of the own rows r >= k, the first on ties; lane k's counts
+    double v = -1.0;
+    int b = 0;
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        const double ov = __shfl_xor(v, off, 64);
-        const int op = __shfl_xor(p, off, 64);
-        if (ov > v || (ov == v && op < p)) {
-          v = ov;
-          p = op;
-        }
-      }
-      if (c == 0 && !(v > tiny)) scal[kSlotPivot] = 1.0;
-      if (p != k && c < m) {
-        double u = A[k][c]; A[k][c] = A[p][c]; A[p][c] = u;
-        u = B[k][c]; B[k][c] = B[p][c]; B[p][c] = u;
+    for (int i = 0; i < R; ++i) {
+      const bool g = (w + i * kGjWaves >= kl) & (fabs(A[i]) > v);
+      v = g ? fabs(A[i]) : v;
+      b = g ? i : b;
+    }
+    v = lane_value(v, k);
+    b = __builtin_amdgcn_readlane(b, k);
+    const int bl = per_lane(b), il = per_lane(k / kGjWaves);
+    double best = A[0];
+#pragma unroll
+    for (int i = 1; i < R; ++i) best = bl == i ? A[i] : best;
+    row[h][w][c] = best;
+    if (w == k % kGjWaves) {
+      double own = A[0];
+#pragma unroll
+      for (int i = 1; i < R; ++i) own = il == i ? A[i] : own;
+      row[h][kGjWaves][c] = own;
+    }
+    // row k itself where no candidate is a number
+    if (c == 0) cand[h][w] = {v, v < 0.0 ? k : w + b * kGjWaves, v < 0.0 ? kGjWaves : w};
+    double fac[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) fac[i] = lane_value(A[i], k);
+    __syncthreads();
+    PivotCand win = cand[h][c & (kGjWaves - 1)];
+    double ka = row[h][kGjWaves][c];
+    better_of_two<0xB1>(win);   // lanes 1 0 3 2
+    better_of_two<0x4E>(win);   // lanes 2 3 0 1
+    better_of_two<0x141>(win);  // the other four of eight
+    const int p = __builtin_amdgcn_readfirstlane(win.p);
+    double pa = row[h][__builtin_amdgcn_readfirstlane(win.w)][c];
+    if (t == 0 && !(win.v > tiny)) scal[kSlotPivot] = 1.0;
+    const double pv = lane_value(pa, k), kk = lane_value(ka, k);
+    const bool in_k = c == kl;  // the inverse's column enters: 1 in the pivot row
+    const double ra = (in_k ? 1.0 : pa) / pv;
+    ka = in_k ? 0.0 : ka;
+#pragma unroll
+    for (int i = 0; i < R; ++i) A[i] = in_k ? 0.0 : A[i];
+    if (w == p % kGjWaves) {  // row k goes to row p's place
+      const int pl = per_lane(p / kGjWaves);
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        A[i] = pl == i ? ka : A[i];
+        fac[i] = pl == i ? kk : fac[i];
       }
     }
-    __syncthreads();
-    if (w == 0 && c < m) {
-      const double pv = A[k][k];
-      rowa[c] = A[k][c] / pv;
-      rowb[c] = B[k][c] / pv;
-      fac[c] = A[c][k];
+#pragma unroll
+    for (int i = 0; i < R; ++i) A[i] -= fac[i] * ra;
+    if (w == k % kGjWaves) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) A[i] = il == i ? ra : A[i];
     }
-    __syncthreads();
-    if (c < m) {
-      const double ra = rowa[c], rb = rowb[c];
-      for (int r = w; r < m; r += kInvWaves) {
-        if (r == k) {
-          A[k][c] = ra;
-          B[k][c] = rb;
-        } else {
-          A[r][c] -= fac[r] * ra;
-          B[r][c] -= fac[r] * rb;
-        }
-      }
-    }
-    __syncthreads();
+    const int fk = __builtin_amdgcn_readlane(from, k), fp = __builtin_amdgcn_readlane(from, p);
+    from = c == p ? fk : from;
+    from = in_k ? fp : from;
   }
   // column-major: entry (r, c) of the inverse at c * m + r, so that the
   // coarsest solve's threads (one per row) read a column together
-  if (c < m)
-    for (int r = w; r < m; r += kInvWaves) inv[c * m + r] = B[r][c];
+  if (c < m) {
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+      if (w + i * kGjWaves < m) inv[from * m + w + i * kGjWaves] = A[i];
+  }
 }
 
 // A coarsest level of up to kMaxCoarseNodes nodes (a grid whose halving
@@ -1304,12 +1363,12 @@ __device__ void coarse_inverse_band_body(const InvArgs &a) {
   }
 }
 
-__global__ __launch_bounds__(kInvThreads) void k_coarse_inverse(InvArgs a) {
+__global__ __launch_bounds__(kGjThreads) void k_coarse_inverse(InvArgs a) {
   coarse_inverse_body(a.st, a.dir, a.nx, a.ny, a.inv, a.cidx, a.scal);
 }
 
 // Batched form: one workgroup per problem.
-__global__ __launch_bounds__(kInvThreads) void k_coarse_inverse_b(BatchTab tab) {
+__global__ __launch_bounds__(kGjThreads) void k_coarse_inverse_b(BatchTab tab) {
   const InvArgs a = *static_cast<const InvArgs *>(tab.e[blockIdx.x].args);
   coarse_inverse_body(a.st, a.dir, a.nx, a.ny, a.inv, a.cidx, a.scal);
 }
@@ -2494,7 +2553,7 @@ hipError_t launch_coarse_inverse(tomg_problem *p) {
   if (p->cband)
     hipLaunchKernelGGL(k_coarse_inverse_band, 1, kInvThreads, 0, p->stream, p->hargs.inv);
   else
-    hipLaunchKernelGGL(k_coarse_inverse, 1, kInvThreads, 0, p->stream, p->hargs.inv);
+    hipLaunchKernelGGL(k_coarse_inverse, 1, kGjThreads, 0, p->stream, p->hargs.inv);
   p->inv_pending = false;
   return hipGetLastError();
 }
@@ -2503,7 +2562,7 @@ void batch_coarse_inverse(tomg_problem *const *probs, const int *idx, int cnt, h
   BatchTab tab;
   tab.count = 0;
   auto flush = [&] {
-    if (tab.count) hipLaunchKernelGGL(k_coarse_inverse_b, tab.count, kInvThreads, 0, s, tab);
+    if (tab.count) hipLaunchKernelGGL(k_coarse_inverse_b, tab.count, kGjThreads, 0, s, tab);
     tab.count = 0;
   };
   for (int k = 0; k < cnt; ++k) {
