@@ -734,6 +734,31 @@ constexpr int kGFX = 2 * kGX + 1, kGFY = 2 * kGY + 1;  // fine stencil window
 constexpr int kGDX = 2 * kGX + 5, kGDY = 2 * kGY + 5;  // fine flag window
 constexpr int kGCX = kGX + 2, kGCY = kGY + 2;          // coarse flag window
 
+// A thread's part of the fine flag window, at (2 I0 - 3 + x, 2 J0 - 3 + y);
+// outside the grid counts as Dirichlet.  Loaded into registers first, all in
+// flight together with what else the block stages.
+template <int NT>
+struct FineFlags {
+  static constexpr int N = (kGDX * kGDY + NT - 1) / NT;
+  uint8_t d[N];
+  __device__ __forceinline__ void load(const uint8_t *dirf, int I0, int J0, int nxf, int nyf,
+                                       int t) {
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      const int k = min(t + q * NT, kGDX * kGDY - 1);
+      const int fi = 2 * I0 - 3 + k % kGDX, fj = 2 * J0 - 3 + k / kGDX;
+      const bool in = fi >= 0 && fj >= 0 && fi < nxf && fj < nyf;
+      const uint8_t v = dirf[in ? (size_t)fj * nxf + fi : 0];
+      d[q] = in ? v : 1;
+    }
+  }
+  __device__ __forceinline__ void store(uint8_t *DF, int t) const {
+#pragma unroll
+    for (int q = 0; q < N; ++q)
+      if (t + q * NT < kGDX * kGDY) DF[t + q * NT] = d[q];
+  }
+};
+
 template <class Op>
 __global__ __launch_bounds__(kGX *kGY) void k_coarsen(Op opf, const uint8_t *dirf, int nxf,
                                                       int nyf, int nxc, int nyc, uint8_t *dirc,
@@ -743,13 +768,22 @@ __global__ __launch_bounds__(kGX *kGY) void k_coarsen(Op opf, const uint8_t *dir
   __shared__ uint8_t DC[kGCY][kGCX];
   constexpr int NT = kGX * kGY;
   const int t = threadIdx.x;
-  const int I0 = blockIdx.x * kGX, J0 = blockIdx.y * kGY;
-  // fine flags at (2 I0 - 3 + x, 2 J0 - 3 + y); outside the grid counts as Dirichlet
-  for (int k = t; k < kGDX * kGDY; k += NT) {
-    const int x = k % kGDX, y = k / kGDX;
-    const int fi = 2 * I0 - 3 + x, fj = 2 * J0 - 3 + y;
-    DF[y][x] = (fi < 0 || fj < 0 || fi >= nxf || fj >= nyf) ? 1 : dirf[(size_t)fj * nxf + fi];
+  int bx, by;
+  xcd_tile(blockIdx.x, (nxc + kGX - 1) / kGX, (nyc + kGY - 1) / kGY, bx, by);
+  const int I0 = bx * kGX, J0 = by * kGY;
+  FineFlags<NT> flags;
+  flags.load(dirf, I0, J0, nxf, nyf, t);
+  // fine stencils at (2 I0 - 1 + x, 2 J0 - 1 + y)
+  constexpr int NS = (kGFX * kGFY + NT - 1) / NT;
+  double s[NS][9];
+#pragma unroll
+  for (int q = 0; q < NS; ++q) {
+    const int k = min(t + q * NT, kGFX * kGFY - 1);
+    const int fi = min(max(2 * I0 - 1 + k % kGFX, 0), nxf - 1);
+    const int fj = min(max(2 * J0 - 1 + k / kGFX, 0), nyf - 1);
+    opf.full((size_t)fj * nxf + fi, s[q]);
   }
+  flags.store(&DF[0][0], t);
   __syncthreads();
   // coarse flags at (I0 - 1 + x, J0 - 1 + y); support of coarse x at fine 2x + 1 + a
   for (int k = t; k < kGCX * kGCY; k += NT) {
@@ -772,25 +806,22 @@ __global__ __launch_bounds__(kGX *kGY) void k_coarsen(Op opf, const uint8_t *dir
     }
     DC[y][x] = d;
   }
-  // fine stencils at (2 I0 - 1 + x, 2 J0 - 1 + y) = flag window (x + 2, y + 2);
-  // a non-Dirichlet fine node is interior or on a Neumann edge, where the
-  // stored stencil has no coefficient outside the grid
-  for (int k = t; k < kGFX * kGFY; k += NT) {
-    const int x = k % kGFX, y = k / kGFX;
-    double s[9];
+  // in the flag window the stencils are at (x + 2, y + 2); a non-Dirichlet
+  // fine node is interior or on a Neumann edge, where the stored stencil has
+  // no coefficient outside the grid
 #pragma unroll
-    for (int q = 0; q < 9; ++q) s[q] = 0.0;
-    if (!DF[y + 2][x + 2]) {
-      const int fi = 2 * I0 - 1 + x, fj = 2 * J0 - 1 + y;
-      opf.full((size_t)fj * nxf + fi, s);
+  for (int z = 0; z < NS; ++z) {
+    const int k = t + z * NT, x = k % kGFX, y = k / kGFX;
+    if (k < kGFX * kGFY) {
+      const bool dirichlet = DF[y + 2][x + 2];
 #pragma unroll
       for (int q = -1; q <= 1; ++q)
 #pragma unroll
-        for (int pp = -1; pp <= 1; ++pp)
-          if (DF[y + 2 + q][x + 2 + pp]) s[(q + 1) * 3 + pp + 1] = 0.0;
+        for (int pp = -1; pp <= 1; ++pp) {
+          const int o = (q + 1) * 3 + pp + 1;
+          S[o][y][x] = dirichlet || DF[y + 2 + q][x + 2 + pp] ? 0.0 : s[z][o];
+        }
     }
-#pragma unroll
-    for (int q = 0; q < 9; ++q) S[q][y][x] = s[q];
   }
   __syncthreads();
   const int tx = t % kGX, ty = t / kGX;
@@ -847,8 +878,11 @@ __global__ __launch_bounds__(kGX *kGY) void k_coarsen(Op opf, const uint8_t *dir
 // EpsOp::coefs, so the products and their order are those of k_coarsen).
 constexpr int kGEX = 2 * kGX + 3, kGEY = 2 * kGY + 3;  // tensor window, origin 2 I0 - 2
 
-// Three waves per SIMD (at most 168 VGPRs instead of 172): 371 -> 286 us at
-// 4097^2; four (128 VGPRs, spilling) took 520 us.
+// Three waves per SIMD (at most 168 VGPRs; four, 128 and spilling, nearly
+// double the time).  All loads of a block are in flight at once, flags and
+// tensor: window by window, five and six at a time, a block spent its time in
+// memory latencies (4097^2 287 -> 197 us, 2049^2 78 -> 52 us; 0.74 GB, 3.7
+// TB/s).  Neighbouring tiles on one XCD, as in k_coarsen, gave nothing here.
 __global__ __launch_bounds__(kGX *kGY, 3) void k_coarsen_eps(EpsOp<double> op, const uint8_t *dirf,
                                                           int nxf, int nyf, int nxc, int nyc,
                                                           uint8_t *dirc, double *stc,
@@ -859,19 +893,26 @@ __global__ __launch_bounds__(kGX *kGY, 3) void k_coarsen_eps(EpsOp<double> op, c
   constexpr int NT = kGX * kGY;
   const int t = threadIdx.x;
   const int I0 = blockIdx.x * kGX, J0 = blockIdx.y * kGY;
-  for (int k = t; k < kGDX * kGDY; k += NT) {
-    const int x = k % kGDX, y = k / kGDX;
-    const int fi = 2 * I0 - 3 + x, fj = 2 * J0 - 3 + y;
-    DF[y][x] = (fi < 0 || fj < 0 || fi >= nxf || fj >= nyf) ? 1 : dirf[(size_t)fj * nxf + fi];
-  }
-  for (int k = t; k < kGEX * kGEY; k += NT) {
-    const int x = k % kGEX, y = k / kGEX;
+  FineFlags<NT> flags;
+  flags.load(dirf, I0, J0, nxf, nyf, t);
+  constexpr int NE = (kGEX * kGEY + NT - 1) / NT;
+  double e[3][NE];
+#pragma unroll
+  for (int q = 0; q < NE; ++q) {
+    const int k = min(t + q * NT, kGEX * kGEY - 1), x = k % kGEX, y = k / kGEX;
     const int fi = min(max(2 * I0 - 2 + x, 0), nxf - 1), fj = min(max(2 * J0 - 2 + y, 0), nyf - 1);
     const size_t c = (size_t)fj * nxf + fi;
-    E[0][y][x] = op.exx[c];
-    E[1][y][x] = op.exy[c];
-    E[2][y][x] = op.eyy[c];
+    e[0][q] = op.exx[c];
+    e[1][q] = op.exy[c];
+    e[2][q] = op.eyy[c];
   }
+  flags.store(&DF[0][0], t);
+#pragma unroll
+  for (int q = 0; q < NE; ++q)
+    if (t + q * NT < kGEX * kGEY) {
+#pragma unroll
+      for (int z = 0; z < 3; ++z) (&E[z][0][0])[t + q * NT] = e[z][q];
+    }
   __syncthreads();
   for (int k = t; k < kGCX * kGCY; k += NT) {
     const int x = k % kGCX, y = k / kGCX;
@@ -2537,7 +2578,7 @@ hipError_t launch_hierarchy(tomg_problem *p, bool defer_inverse) {
       hipLaunchKernelGGL(k_coarsen_eps, grid, kGX * kGY, 0, p->stream, op64(p), lf.dir, lf.nx,
                          lf.ny, lc.nx, lc.ny, lc.dir, lc.st, st32);
     else
-      hipLaunchKernelGGL((k_coarsen<StOp<double>>), grid, kGX * kGY, 0, p->stream,
+      hipLaunchKernelGGL((k_coarsen<StOp<double>>), grid.x * grid.y, kGX * kGY, 0, p->stream,
                          st_op<double>(lf.st, lf.nx, lf.ny), lf.dir, lf.nx, lf.ny, lc.nx, lc.ny,
                          lc.dir, lc.st, st32);
   }
