@@ -190,6 +190,25 @@ __device__ __forceinline__ void record_history(double *scal, int rel, double r) 
   if (c >= 0 && c < kHistMax) scal[kNumSlots + c] = r;
 }
 
+// v combined with a thread's partials, in their order.  The loads of eight are
+// in flight together: one at a time, the few partials of a thread cost a
+// memory latency each (8.6 thousand partials 15.5 -> 6.7 us, 1 thousand 4.6
+// -> 3.9 us).
+template <int OP>
+__device__ __forceinline__ double combine_strided(double v, const double *partials, int n,
+                                                  int stride) {
+  for (int k = threadIdx.x; k < n; k += 8 * blockDim.x) {
+    double p[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      p[j] = partials[(size_t)min(k + j * (int)blockDim.x, n - 1) * stride];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (k + j * (int)blockDim.x < n) v = combine<OP>(v, p[j]);
+  }
+  return v;
+}
+
 // One block: fixed-order reduction of n partials into out[0].
 // OP 0 sum, 1 min, 2 max; do_sqrt takes the square root of the result.
 // rel == kRelBegin (the initial norms of a solve): out[0] is also recorded as
@@ -202,8 +221,7 @@ __global__ void k_finalize(const double *partials, int n, int stride, double *ou
                            double *scal, int rel, const double *skip) {
   if (skip && *skip != 0.0) return;
   double v = OP == 0 ? 0.0 : (OP == 1 ? INFINITY : -INFINITY);
-  for (int k = threadIdx.x; k < n; k += blockDim.x) v = combine<OP>(v, partials[(size_t)k * stride]);
-  v = block_reduce<OP>(v);
+  v = block_reduce<OP>(combine_strided<OP>(v, partials, n, stride));
   if (threadIdx.x == 0) {
     if (do_sqrt) v = sqrt(v);
     out[0] = v;
@@ -2072,8 +2090,7 @@ __global__ void k_finalize_b(BatchTab tab, int rel, double *out) {
   const BatchEntry &e = tab.e[blockIdx.x];
   const FinArgs a = *static_cast<const FinArgs *>(e.args);
   double v = 0.0;
-  for (int k = threadIdx.x; k < a.n; k += blockDim.x) v += a.partials[k];
-  v = block_reduce<0>(v);
+  v = block_reduce<0>(combine_strided<0>(v, a.partials, a.n, 1));
   if (threadIdx.x == 0) {
     v = sqrt(v);
     a.scal[e.slot] = v;
