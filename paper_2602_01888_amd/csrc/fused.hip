@@ -772,9 +772,12 @@ static void launch_updown(int nu, const PassArgs<T> &a, hipStream_t s) {
 // from the tensor the level-0 pass is bound by its steps' phase chain, not
 // by its bytes, and the chained pass's sixteen colour phases per step made
 // it slower than the two passes it replaces (295 against 135 + 134 us).
+// Nor where level 0 is on tiles (semi-annulus, FP32: 1025^2 64 us chained
+// against 22 + 23, 513^2 46 against 8 + 10).
 bool chain_inner(const tomg_problem *p) {
   return p->cfg.precision == TOMG_FP32_IR && p->cfg.smoother == TOMG_GS4 && p->L >= 2 &&
-         p->cfg.nu1 + p->cfg.nu2 <= 4 && stored_level0(p->cfg);
+         p->cfg.nu1 + p->cfg.nu2 <= 4 && stored_level0(p->cfg) &&
+         !(on_tiles(p->hargs.up32[0]) && on_tiles(p->hargs.down32[0]));
 }
 
 // Arguments of the down (up) pass of level l in precision T: the level

@@ -30,8 +30,9 @@ struct Halo {  // nodes around the owned tile (even, so that quads stay whole)
   static constexpr int S = 2 * NU + (RES ? 2 : 0), N = 2 * NU;
 };
 
+// CK, the grid transfer: 0 both axes halved, 1 x halved alone, 2 y halved alone.
 template <typename T, bool EPS, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, int QX,
-          int QY>
+          int QY, int CK>
 __device__ __forceinline__ void tile_body(const PassArgs<T> &a, const int bx, const int by) {
   using H = Halo<NU, RESTRICT || NORM>;
   constexpr int PITCH = QX + 2, PS = PITCH * (QY + 2);
@@ -121,7 +122,32 @@ __device__ __forceinline__ void tile_body(const PassArgs<T> &a, const int bx, co
 #pragma unroll
     for (int k = 0; k < 4; ++k) dg[k] = q.a[k][4];
   }
-  if constexpr (PROLONG) {
+  if constexpr (PROLONG && CK != 0) {
+    T e[4];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {  // along the halved axis: at the coarse node, half way
+      T c0, c1;
+      int k0, k1;
+      if constexpr (CK == 1) {  // row j0 + b
+        const T *r0 = a.xc + (size_t)min(max(j0 + b, 0), a.nyc - 1) * a.nxc;
+        const int I = min(max(i0 >> 1, 0), a.nxc - 1);
+        c0 = r0[I];
+        c1 = r0[min(I + 1, a.nxc - 1)];
+        k0 = 2 * b, k1 = 2 * b + 1;
+      } else {  // column i0 + b
+        const T *r0 = a.xc + min(max(i0 + b, 0), a.nxc - 1);
+        const int J = min(max(j0 >> 1, 0), a.nyc - 1);
+        c0 = r0[(size_t)J * a.nxc];
+        c1 = r0[(size_t)min(J + 1, a.nyc - 1) * a.nxc];
+        k0 = b, k1 = b + 2;
+      }
+      e[k0] = c0;
+      e[k1] = T(0.5) * (c0 + c1);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (q.ik[k] != T(0)) q.x[k] += e[k];
+  } else if constexpr (PROLONG) {
     const int I = min(max(i0 >> 1, 0), a.nxc - 1), J = min(max(j0 >> 1, 0), a.nyc - 1);
     const int I1 = min(I + 1, a.nxc - 1), J1 = min(J + 1, a.nyc - 1);
     const T *r0 = a.xc + (size_t)J * a.nxc, *r1 = a.xc + (size_t)J1 * a.nxc;
@@ -169,7 +195,20 @@ __device__ __forceinline__ void tile_body(const PassArgs<T> &a, const int bx, co
 #pragma unroll
     for (int k = 0; k < 4; ++k) c[k * PS] = res[k];
     __syncthreads();
-    if (own && in[0]) {
+    if constexpr (CK != 0) {  // (1/4) [1 2 1] along the halved axis, two coarse nodes
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const int k = CK == 1 ? 2 * b : b;
+        if (own && in[k]) {
+          const int I = CK == 1 ? i0 >> 1 : i0 + b, J = CK == 1 ? j0 + b : j0 >> 1;
+          const bool ring = I == 0 || J == 0 || I == a.nxc - 1 || J == a.nyc - 1;
+          const bool fixed = ring && (!a.dirc || a.dirc[(size_t)J * a.nxc + I]);
+          const T lo = quad_nb(res, c, k, CK == 1 ? -1 : 0, CK == 1 ? 0 : -1, PS, PITCH);
+          const T hi = quad_nb(res, c, k, CK == 1 ? 1 : 0, CK == 1 ? 0 : 1, PS, PITCH);
+          a.bc[(size_t)J * a.nxc + I] = fixed ? T(0) : (lo + T(2) * res[k] + hi) * T(0.25);
+        }
+      }
+    } else if (own && in[0]) {
       const int I = i0 >> 1, J = j0 >> 1;
       const bool ring = I == 0 || J == 0 || I == a.nxc - 1 || J == a.nyc - 1;
       // a coarse ring node is Dirichlet unless its edge is Neumann
@@ -191,48 +230,57 @@ __device__ __forceinline__ void tile_body(const PassArgs<T> &a, const int bx, co
 }
 
 template <typename T, bool EPS, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, int QX,
-          int QY>
+          int QY, int CK>
 __global__ __launch_bounds__(QX *QY) void k_tile(PassArgs<T> a) {
   if (a.skip && *a.skip != 0.0) return;
-  tile_body<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, QX, QY>(a, blockIdx.x % a.nbx,
-                                                              blockIdx.x / a.nbx);
+  tile_body<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, QX, QY, CK>(a, blockIdx.x % a.nbx,
+                                                                  blockIdx.x / a.nbx);
 }
 
 template <typename T, bool EPS, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, int QX,
-          int QY>
+          int QY, int CK>
 __global__ __launch_bounds__(QX *QY) void k_tile_b(BatchTab tab) {
   int bx, by;
   const PassArgs<T> a = batch_args<T>(tab, bx, by);
-  tile_body<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, QX, QY>(a, bx, by);
+  tile_body<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, QX, QY, CK>(a, bx, by);
 }
 
 template <typename T, bool EPS, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, int QX,
-          int QY>
+          int QY, int CK>
 void launch_shape(const PassArgs<T> &a, hipStream_t s, const BatchTab *tab, int nb) {
   if (tab)
-    hipLaunchKernelGGL((k_tile_b<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, QX, QY>), nb, QX * QY,
-                       0, s, *tab);
+    hipLaunchKernelGGL((k_tile_b<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, QX, QY, CK>), nb,
+                       QX * QY, 0, s, *tab);
   else
-    hipLaunchKernelGGL((k_tile<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, QX, QY>), a.nbx * a.nby,
-                       QX * QY, 0, s, a);
+    hipLaunchKernelGGL((k_tile<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, QX, QY, CK>),
+                       a.nbx * a.nby, QX * QY, 0, s, a);
 }
-template <typename T, bool EPS, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
+template <typename T, bool EPS, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, int CK>
 void launch_nu(int nu, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab, int nb) {
   const bool large = a.form == kFormTileLarge;
   if (nu == 1 && large)
-    launch_shape<T, EPS, 1, ZERO, PROLONG, RESTRICT, NORM, 32, 16>(a, s, tab, nb);
+    launch_shape<T, EPS, 1, ZERO, PROLONG, RESTRICT, NORM, 32, 16, CK>(a, s, tab, nb);
   else if (nu == 1)
-    launch_shape<T, EPS, 1, ZERO, PROLONG, RESTRICT, NORM, 16, 16>(a, s, tab, nb);
+    launch_shape<T, EPS, 1, ZERO, PROLONG, RESTRICT, NORM, 16, 16, CK>(a, s, tab, nb);
   else if (large)
-    launch_shape<T, EPS, 2, ZERO, PROLONG, RESTRICT, NORM, 32, 16>(a, s, tab, nb);
+    launch_shape<T, EPS, 2, ZERO, PROLONG, RESTRICT, NORM, 32, 16, CK>(a, s, tab, nb);
   else
-    launch_shape<T, EPS, 2, ZERO, PROLONG, RESTRICT, NORM, 16, 16>(a, s, tab, nb);
+    launch_shape<T, EPS, 2, ZERO, PROLONG, RESTRICT, NORM, 16, 16, CK>(a, s, tab, nb);
+}
+template <typename T, bool EPS, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
+void launch_ck(int nu, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab, int nb) {
+  if (a.ck == 0)
+    launch_nu<T, EPS, ZERO, PROLONG, RESTRICT, NORM, 0>(nu, a, s, tab, nb);
+  else if (a.ck == 1)
+    launch_nu<T, EPS, ZERO, PROLONG, RESTRICT, NORM, 1>(nu, a, s, tab, nb);
+  else
+    launch_nu<T, EPS, ZERO, PROLONG, RESTRICT, NORM, 2>(nu, a, s, tab, nb);
 }
 
 }  // namespace
 
-// Gives the pass the tile form where it is the faster one: alone, both axes
-// halved, at most two sweeps (the halo of four is wider than the tile).
+// Gives the pass the tile form where it is the faster one: alone, at most two
+// sweeps (the halo of four is wider than the tile).
 // Measured per pass (down, up; V(2,2), FP64, a cycle of 4097^2), marching
 // -> tiles: 65^2 13.1, 14.1 -> 5.8, 5.3 us; 129^2 12.9, 12.4 -> 6.2, 5.8;
 // 257^2 14.7, 16.4 -> 7.9, 6.2; 513^2 21.7, 22.0 -> 15.7, 12.6; 1025^2 39.1,
@@ -245,13 +293,16 @@ void launch_nu(int nu, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab,
 // still, are the faster from 257^2 up (256 problems of sides 65 .. 1025, mixed
 // precision: no tiles 23.87 ms, up to 65^2 23.63, 129^2 23.50, 257^2 24.98,
 // 513^2 26.34; FP64 34.10, 33.45, 32.52, 34.00, 34.90).
+// One axis halved (semi-annulus of 1537 x 769, stored, FP32; bands -> tiles):
+// level 1, 769 x 769, 23, 22 -> 14, 14 us; level 0, whose bands ran chained
+// in 66 us with the next cycle's downward pass, 23 + 27.
 constexpr long kTileNodes = 1200000;      // largest level on tiles
 constexpr long kSmallTileNodes = 20000;   // largest level on 32 x 32 tiles
 constexpr long kTileNodesBatch = 20000;   // largest level on tiles in a batch
 template <typename T>
 bool pick_tile(PassArgs<T> &a, int nu, bool res, bool batch) {
   const long n = (long)a.nx * a.ny;
-  if (nu > 2 || a.ck != 0 || n > (batch ? kTileNodesBatch : kTileNodes)) return false;
+  if (nu > 2 || n > (batch ? kTileNodesBatch : kTileNodes)) return false;
   a.form = n > kSmallTileNodes ? kFormTileLarge : kFormTileSmall;
   const int hx = 8 * nu + (res ? 2 : 0), hy = 4 * nu + (res ? 2 : 0);
   a.W = (a.form == kFormTileLarge ? 64 : 32) - hx;
@@ -267,21 +318,21 @@ template bool pick_tile<float>(PassArgs<float> &, int, bool, bool);
 template <typename T>
 void tile_down(int nu, bool eps, bool zero, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab, int nb) {
   if (eps) {
-    if (zero) launch_nu<T, true, true, false, true, false>(nu, a, s, tab, nb);
-    else launch_nu<T, true, false, false, true, false>(nu, a, s, tab, nb);
+    if (zero) launch_ck<T, true, true, false, true, false>(nu, a, s, tab, nb);
+    else launch_ck<T, true, false, false, true, false>(nu, a, s, tab, nb);
   } else {
-    if (zero) launch_nu<T, false, true, false, true, false>(nu, a, s, tab, nb);
-    else launch_nu<T, false, false, false, true, false>(nu, a, s, tab, nb);
+    if (zero) launch_ck<T, false, true, false, true, false>(nu, a, s, tab, nb);
+    else launch_ck<T, false, false, false, true, false>(nu, a, s, tab, nb);
   }
 }
 template <typename T>
 void tile_up(int nu, bool eps, bool norm, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab, int nb) {
   if (eps) {
-    if (norm) launch_nu<T, true, false, true, false, true>(nu, a, s, tab, nb);
-    else launch_nu<T, true, false, true, false, false>(nu, a, s, tab, nb);
+    if (norm) launch_ck<T, true, false, true, false, true>(nu, a, s, tab, nb);
+    else launch_ck<T, true, false, true, false, false>(nu, a, s, tab, nb);
   } else {
-    if (norm) launch_nu<T, false, false, true, false, true>(nu, a, s, tab, nb);
-    else launch_nu<T, false, false, true, false, false>(nu, a, s, tab, nb);
+    if (norm) launch_ck<T, false, false, true, false, true>(nu, a, s, tab, nb);
+    else launch_ck<T, false, false, true, false, false>(nu, a, s, tab, nb);
   }
 }
 template void tile_down<double>(int, bool, bool, const PassArgs<double> &, hipStream_t, const BatchTab *, int);
