@@ -8,10 +8,18 @@
 //   up pass:   bilinear prolongation and correction on load (eq. 24) + nu
 //              sweeps [+ partial sums of the final residual's squares].
 //
-// Block geometry: BW threads own BW consecutive columns (one each); the
-// H = 4 nu + 2 outer columns on either side are halo, recomputed by the
-// neighbouring block, so only W = BW - 2H columns are written.  BW is 128
-// (two waves), 64 (one wave) on the stored-stencil levels of a problem
+// Three forms do this, bitwise alike (quad.h has the arithmetic); this file
+// holds the launches of all and the band form, which takes any sweep count
+// and grid transfer.  Up to two sweeps the others are faster and have most of
+// the work: whole tiles on small and middle levels (tile.hip), one wave
+// marching on large ones (march.hip).  The bands keep three and four sweeps,
+// semi-coarsened transfers of large levels and of batches, and the chained
+// pass of the FP32 inner cycles.
+//
+// Block geometry of the band form: BW threads own BW consecutive columns (one
+// each); the H = 4 nu + 2 outer columns on either side are halo, recomputed
+// by the neighbouring block, so only W = BW - 2H columns are written.  BW is
+// 128 (two waves), 64 (one wave) on the stored-stencil levels of a problem
 // alone that are small enough to be bound by the chain of colour phases
 // rather than by memory traffic, and 256 in the chained pass.  The block
 // owns a band of CH rows and marches up it two rows at a time, starting
@@ -47,7 +55,8 @@ namespace {
 // Block widths.  A colour phase ends in a barrier over the block's waves, so
 // narrower blocks shorten each step's chain of phases and give the device
 // more blocks, at the cost of more recomputed halo columns (2H of BW).
-// Measured per pass at 4097^2, FP64, four-wave -> two-wave blocks: level 0
+// Measured per pass of two sweeps, both axes halved (passes that now have the
+// other forms), at 4097^2, FP64, four-wave -> two-wave blocks: level 0
 // down 250 -> 232 us, up 272 -> 261, 2049^2 119 -> 112 and 101 -> 98; FP32
 // level 0 138 -> 128 and 130 -> 129.  One-wave blocks on the stored levels
 // up to 1025^2 (four-wave -> one-wave): 1025^2 44.7 -> 38.6 us, 513^2 25.9
@@ -568,7 +577,8 @@ __global__ __launch_bounds__(kBWBatch, TOMG_MIN_WAVES) void k_pass_b(BatchTab ta
 // on the 256-problem batch (sides 65-1025, mixed precision): 30.5 ms with 16
 // rows everywhere, 29.1 with 32, 31.8 with 64, 40.8 with 128, 28.2 with this
 // table; on the serving stream (sides 129-2049) it raised the closed-loop
-// capacity by 6 %.
+// capacity by 6 %.  (With the passes in LDS bands; the marching passes of a
+// batch on bands 1.5 .. 3 times as tall: 23.3 -> 23.9 .. 25.3 ms.)
 constexpr int kMinBand = 2;
 int pick_band_batch(int ny) {
   const int c = ny >= 1025 ? 40 : (ny >= 513 ? 32 : (ny >= 257 ? 24 : 16));

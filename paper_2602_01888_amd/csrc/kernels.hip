@@ -185,8 +185,8 @@ __device__ __forceinline__ double rel_residual(double v, double b0, double r0) {
 // The residual history after the scalar slots: entry 0 at the start of a
 // solve, entry c after its cycle c (cycles counted in kSlotCycles, which
 // the start of a batched solve resets; a single solve resets it itself).
-__device__ __forceinline__ void record_history(double *scal, int rel, double r) {
-  const int c = rel == kRelBegin ? 0 : (int)scal[kSlotCycles];
+__device__ __forceinline__ void record_history(double *scal, int rel, double cycles, double r) {
+  const int c = rel == kRelBegin ? 0 : (int)cycles;
   if (c >= 0 && c < kHistMax) scal[kNumSlots + c] = r;
 }
 
@@ -219,20 +219,29 @@ __device__ __forceinline__ double combine_strided(double v, const double *partia
 template <int OP>
 __global__ void k_finalize(const double *partials, int n, int stride, double *out, int do_sqrt,
                            double *scal, int rel, const double *skip) {
-  if (skip && *skip != 0.0) return;
+  // all that is read, the scalars too, is under way together with the partials:
+  // the launch is the chain of its memory latencies
+  const double stop = skip ? *skip : 0.0;
+  double b0 = 0.0, r0 = 0.0, tol = 0.0, cycles = 0.0;
+  if (rel != kRelNone) {
+    b0 = scal[kSlotB0];
+    r0 = scal[kSlotR0];
+    tol = scal[kSlotTol];
+    cycles = scal[kSlotCycles];
+  }
   double v = OP == 0 ? 0.0 : (OP == 1 ? INFINITY : -INFINITY);
   v = block_reduce<OP>(combine_strided<OP>(v, partials, n, stride));
-  if (threadIdx.x == 0) {
+  if (threadIdx.x == 0 && stop == 0.0) {
     if (do_sqrt) v = sqrt(v);
     out[0] = v;
     if (rel != kRelNone) {
-      if (rel == kRelBegin) scal[kSlotR0] = v;
-      const double r = rel_residual(v, scal[kSlotB0], scal[kSlotR0]);
+      if (rel == kRelBegin) scal[kSlotR0] = r0 = v;
+      const double r = rel_residual(v, b0, r0);
       scal[kSlotRel] = r;
       // a non-finite start also stops cycles queued behind it
-      scal[kSlotDone] = (r <= scal[kSlotTol] || (rel == kRelBegin && !isfinite(r))) ? 1.0 : 0.0;
-      if (rel == kRelCycle) scal[kSlotCycles] += 1.0;
-      record_history(scal, rel, r);
+      scal[kSlotDone] = (r <= tol || (rel == kRelBegin && !isfinite(r))) ? 1.0 : 0.0;
+      if (rel == kRelCycle) scal[kSlotCycles] = cycles += 1.0;
+      record_history(scal, rel, cycles, r);
     }
   }
 }
@@ -2107,7 +2116,7 @@ __global__ void k_finalize_b(BatchTab tab, int rel, double *out) {
       a.scal[kSlotDone] = (r <= a.scal[kSlotTol]) ? 1.0 : 0.0;
       if (rel == kRelBegin) a.scal[kSlotCycles] = 0.0;
       if (rel == kRelCycle) a.scal[kSlotCycles] += 1.0;
-      record_history(a.scal, rel, r);
+      record_history(a.scal, rel, a.scal[kSlotCycles], r);
       out[e.out] = r;
     }
   }

@@ -41,7 +41,7 @@ static_assert(kMaxCoarseNodes <= kMaxCoarseUnknowns * kMaxCoarseUnknowns,
               "the coarsest solve alone keeps its right-hand side where the inverse is staged");
 
 template <typename T, int NT, bool FREE>
-__device__ __forceinline__ void tail_body(const TailArgs<T> &a) {
+__device__ __forceinline__ void tail_body(const TailArgs<T> &a, const double stop) {
   constexpr int OFF = FREE ? 0 : 1;
   constexpr bool KEEP = NT < kTailWide;  // registers for a lower level's quad beside the first's
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -126,6 +126,7 @@ __device__ __forceinline__ void tail_body(const TailArgs<T> &a) {
   const int nco = cl.nx * cl.ny;
   const int m = a.cidx[nco];
   if (nl == 1) {  // the coarsest solve alone (a batch; up to kMaxCoarseNodes nodes)
+    if (stop != 0.0) return;
     for (int c = t; c < nco; c += NT)
       if (a.cidx[c] >= 0) cinv[a.cidx[c]] = (double)cl.b[c];
     __syncthreads();
@@ -138,7 +139,8 @@ __device__ __forceinline__ void tail_body(const TailArgs<T> &a) {
     }
     return;
   }
-  // everything the launch reads from memory, issued together
+  // everything the launch reads from memory, issued together; stop, whose
+  // test would cost the launch another memory latency up front, is tested after
   const int qt = owned(top);
   QuadSt<T> Q, Ql;  // the first level's quad; a lower level's
   int ql = -1, rl = -1;
@@ -166,6 +168,7 @@ __device__ __forceinline__ void tail_body(const TailArgs<T> &a) {
   for (int c = t; c < a.lds; c += NT) S[c] = T(0);
   for (int c = t; c < m * m; c += NT) cinv[c] = a.cinv[c];
   if (t < nco) ci[t] = a.cidx[t];
+  if (stop != 0.0) return;
   __syncthreads();
 
   QuadSt<T> &L = KEEP ? Ql : Q;  // registers of the lower levels
@@ -291,15 +294,15 @@ __device__ __forceinline__ void tail_body(const TailArgs<T> &a) {
 
 template <typename T, int NT, bool FREE>
 __global__ __launch_bounds__(NT) void k_tail(TailArgs<T> a) {
-  if (a.skip && *a.skip != 0.0) return;
-  tail_body<T, NT, FREE>(a);
+  const double stop = a.skip ? *a.skip : 0.0;
+  tail_body<T, NT, FREE>(a, stop);
 }
 
 // Batched form: one workgroup per problem.
 template <typename T, int NT, bool FREE>
 __global__ __launch_bounds__(NT) void k_tail_b(BatchTab tab) {
   const TailArgs<T> &a = *static_cast<const TailArgs<T> *>(tab.e[blockIdx.x].args);
-  tail_body<T, NT, FREE>(a);
+  tail_body<T, NT, FREE>(a, 0.0);
 }
 
 }  // namespace

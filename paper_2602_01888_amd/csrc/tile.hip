@@ -33,7 +33,8 @@ struct Halo {  // nodes around the owned tile (even, so that quads stay whole)
 // CK, the grid transfer: 0 both axes halved, 1 x halved alone, 2 y halved alone.
 template <typename T, bool EPS, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, int QX,
           int QY, int CK>
-__device__ __forceinline__ void tile_body(const PassArgs<T> &a, const int bx, const int by) {
+__device__ __forceinline__ void tile_body(const PassArgs<T> &a, const int bx, const int by,
+                                          const double stop) {
   using H = Halo<NU, RESTRICT || NORM>;
   constexpr int PITCH = QX + 2, PS = PITCH * (QY + 2);
   __shared__ T S[4 * PS];
@@ -158,6 +159,7 @@ __device__ __forceinline__ void tile_body(const PassArgs<T> &a, const int bx, co
     for (int k = 0; k < 4; ++k)
       if (q.ik[k] != T(0)) q.x[k] += e[k];
   }
+  if (stop != 0.0) return;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     if (ZERO || !in[k]) q.x[k] = T(0);
@@ -232,9 +234,11 @@ __device__ __forceinline__ void tile_body(const PassArgs<T> &a, const int bx, co
 template <typename T, bool EPS, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, int QX,
           int QY, int CK>
 __global__ __launch_bounds__(QX *QY) void k_tile(PassArgs<T> a) {
-  if (a.skip && *a.skip != 0.0) return;
+  // tested in the body once the tile's loads are under way: a launch is one
+  // memory latency long, and the test first would be another
+  const double stop = a.skip ? *a.skip : 0.0;
   tile_body<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, QX, QY, CK>(a, blockIdx.x % a.nbx,
-                                                                  blockIdx.x / a.nbx);
+                                                                  blockIdx.x / a.nbx, stop);
 }
 
 template <typename T, bool EPS, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, int QX,
@@ -242,7 +246,7 @@ template <typename T, bool EPS, int NU, bool ZERO, bool PROLONG, bool RESTRICT, 
 __global__ __launch_bounds__(QX *QY) void k_tile_b(BatchTab tab) {
   int bx, by;
   const PassArgs<T> a = batch_args<T>(tab, bx, by);
-  tile_body<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, QX, QY, CK>(a, bx, by);
+  tile_body<T, EPS, NU, ZERO, PROLONG, RESTRICT, NORM, QX, QY, CK>(a, bx, by, 0.0);
 }
 
 template <typename T, bool EPS, int NU, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM, int QX,
