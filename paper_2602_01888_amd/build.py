@@ -10,8 +10,12 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtomg.so")
 SOURCES = ["api.hip", "kernels.hip", "fused.hip", "tile.hip",
            "march.hip", "tail.hip"]
+# the three forms of the level passes, compiled apart, make one object
+# (fused.hip.o): none is of use without the others
+FORMS = ["fused.hip", "tile.hip", "march.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+LLD = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "ld.lld")
 FLAGS = [
     "--offload-arch=gfx950",
     "-O3",
@@ -32,15 +36,16 @@ def sources():
 
 
 def build(verbose: bool = False) -> str:
-    """Compiles every source to an object (in parallel), then links the
-    shared library."""
+    """Compiles every source to an object (in parallel), joins the forms of the
+    level passes, then links the shared library."""
     from concurrent.futures import ThreadPoolExecutor
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
     compile_flags = [f for f in FLAGS if f != "-shared"]
 
     def one(src):
-        obj = os.path.join(objdir, os.path.basename(src) + ".o")
+        name = os.path.basename(src)
+        obj = os.path.join(objdir, name + (".part.o" if name in FORMS else ".o"))
         cmd = [HIPCC] + compile_flags + ["-c", "-o", obj, src]
         if verbose:
             print(" ".join(cmd), flush=True)
@@ -49,6 +54,13 @@ def build(verbose: bool = False) -> str:
 
     with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
         objs = list(ex.map(one, sources()))
+    parts = [o for o in objs if o.endswith(".part.o")]
+    fused = os.path.join(objdir, "fused.hip.o")
+    cmd = [LLD, "-r", "-o", fused] + parts
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    objs = [o for o in objs if o not in parts] + [fused]
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB + ".tmp"] + objs
     if verbose:
         print(" ".join(cmd), flush=True)
