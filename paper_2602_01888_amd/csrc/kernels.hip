@@ -1263,6 +1263,9 @@ __device__ __forceinline__ void coarse_inverse_body(const double *st, const uint
   }
   __syncthreads();
   double A[R];
+  int own[R];  // the wave's rows, -1 past the last: where a column holds only NaN
+               // a zero of those would pass for the pivot, and its row for a column
+               // of the inverse
   const bool in = c < m;
   const int qc = in ? node[c] : 0, Ic = in ? col[c] : 0, Jc = in ? lvl[c] : 0;
 #pragma unroll
@@ -1272,6 +1275,7 @@ __device__ __forceinline__ void coarse_inverse_body(const double *st, const uint
     const bool near = in & (r < m) & (di >= -1) & (di <= 1) & (dj >= -1) & (dj <= 1);
     const double x = st[near ? ((dj + 1) * 3 + di + 1) * n + node[rc] : 0];
     A[i] = near ? x : 0.0;
+    own[i] = r < m ? r : -1;
   }
   // scale of the pivot test: the largest diagonal magnitude; a pivot below
   // 1e-12 of it marks the matrix singular (a problem without Dirichlet nodes,
@@ -1290,7 +1294,7 @@ __device__ __forceinline__ void coarse_inverse_body(const double *st, const uint
     int b = 0;
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-      const bool g = (w + i * kGjWaves >= kl) & (fabs(A[i]) > v);
+      const bool g = (own[i] >= kl) & (fabs(A[i]) > v);
       v = g ? fabs(A[i]) : v;
       b = g ? i : b;
     }
@@ -1302,10 +1306,10 @@ __device__ __forceinline__ void coarse_inverse_body(const double *st, const uint
     for (int i = 1; i < R; ++i) best = bl == i ? A[i] : best;
     row[h][w][c] = best;
     if (w == k % kGjWaves) {
-      double own = A[0];
+      double rk = A[0];
 #pragma unroll
-      for (int i = 1; i < R; ++i) own = il == i ? A[i] : own;
-      row[h][kGjWaves][c] = own;
+      for (int i = 1; i < R; ++i) rk = il == i ? A[i] : rk;
+      row[h][kGjWaves][c] = rk;
     }
     // row k itself where no candidate is a number
     if (c == 0) cand[h][w] = {v, v < 0.0 ? k : w + b * kGjWaves, v < 0.0 ? kGjWaves : w};
