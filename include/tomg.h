@@ -442,11 +442,12 @@ enum {
   TOMG_FIELD_EXY = 1,
   TOMG_FIELD_EYY = 2,
   TOMG_FIELD_DET = 3,
-  TOMG_FIELD_RHS = 4,    /* level 0 f, or level l >= 1 coarse right-hand side */
+  TOMG_FIELD_RHS = 4,    /* level 0 f, or the right-hand side of level l >= 1 in the
+                            last FP64 V-cycle */
   TOMG_FIELD_DIR = 5,    /* uint8 Dirichlet flags of level l */
   TOMG_FIELD_STENCIL = 6,/* level l >= 1, and level 0 with Neumann edges (the folded
                             operator): 9 planes, plane k = (dj+1)*3+(di+1) */
-  TOMG_FIELD_X = 7       /* level l >= 1 correction from the last V-cycle */
+  TOMG_FIELD_X = 7       /* level l >= 1 correction from the last FP64 V-cycle */
 };
 /* Copies array `what` of level `level` into d_out (device); asynchronous. */
 tomg_status tomg_export(tomg_problem *p, int32_t what, int32_t level, void *d_out);

@@ -37,6 +37,8 @@ namespace {
 constexpr int kTailWide = 1024, kTailNarrow = 512;  // threads of the two forms
 constexpr int kTailMaxNodes = 65 * 65;              // per level
 constexpr int kTailLdsMax = 160 * 1024 - 2 * 1024;
+constexpr int kRhsThread = 128;  // first thread of the waves idle in the coarsest solve
+static_assert(kSmallCoarseNodes <= kRhsThread, "a thread per node of the coarsest level");
 static_assert(kMaxCoarseNodes <= kMaxCoarseUnknowns * kMaxCoarseUnknowns,
               "the coarsest solve alone keeps its right-hand side where the inverse is staged");
 
@@ -232,6 +234,14 @@ __device__ __forceinline__ void tail_body(const TailArgs<T> &a, const double sto
         for (int q = 0; q < m; ++q) s += cinv[q * m + k] * bb[q];
       S[cl.xoff + t] = (T)s;
       cl.x[t] = (T)s;
+    } else if (std::is_same<T, double>::value && t >= kRhsThread) {
+      // right-hand sides that only LDS holds, for callers that export them, by
+      // waves that have no part in the coarsest solve
+      for (int r = nl - 2; r >= 0; --r) {
+        const TailLevel<T> &v = lvl(r);
+        for (int c = t - kRhsThread; c < v.nx * v.ny; c += NT - kRhsThread)
+          v.b[c] = S[v.foff + c];
+      }
     }
     __syncthreads();
   }
@@ -340,7 +350,7 @@ static bool make_tail_args(const tomg_problem *p, int lc, TailArgs<T> &a) {
     e.ny = v.ny;
     e.st = (const T *)(f32 ? (void *)v.st32 : (void *)v.st);
     e.x = (T *)(f32 ? (void *)v.x32 : (void *)v.x);
-    e.b = (const T *)(f32 ? (void *)v.b32 : (void *)v.b);
+    e.b = (T *)(f32 ? (void *)v.b32 : (void *)v.b);
     e.dir = v.dir;
     const bool coarsest = q == a.nl - 1;
     e.qx = (v.nx + 1 - off) / 2;

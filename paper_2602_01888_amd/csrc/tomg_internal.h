@@ -102,7 +102,7 @@ struct TailLevel {
   int nx, ny;
   const T *st;
   T *x;
-  const T *b;
+  T *b;           // read on the first level, written on the others (FP64)
   const uint8_t *dir;
   int qx, nq;     // quads per row, and in all
   int pitch, ps;  // row pitch and size of an LDS plane (a ring of zeros around the quads)
