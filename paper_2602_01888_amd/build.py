@@ -15,7 +15,9 @@ SOURCES = ["api.hip", "kernels.hip", "fused.hip", "tile.hip",
 FORMS = ["fused.hip", "tile.hip", "march.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-LLD = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "ld.lld")
+OBJDIR = os.path.join(HERE, "_build")
+HEADERS = [os.path.join(CSRC, "tomg_internal.h"), os.path.join(CSRC, "quad.h"),
+           os.path.join(ROOT, "include", "tomg.h")]
 FLAGS = [
     "--offload-arch=gfx950",
     "-O3",
@@ -35,17 +37,27 @@ def sources():
     return [os.path.join(CSRC, s) for s in SOURCES]
 
 
+def object_of(name):
+    """The object a source is compiled to."""
+    return os.path.join(OBJDIR, name + (".part.o" if name in FORMS else ".o"))
+
+
+def linker():
+    """The linker that goes with the compiler in use."""
+    out = subprocess.run([HIPCC, "-print-prog-name=ld.lld"], check=True, capture_output=True,
+                         text=True)
+    return out.stdout.strip()
+
+
 def build(verbose: bool = False) -> str:
     """Compiles every source to an object (in parallel), joins the forms of the
     level passes, then links the shared library."""
     from concurrent.futures import ThreadPoolExecutor
-    objdir = os.path.join(HERE, "_build")
-    os.makedirs(objdir, exist_ok=True)
+    os.makedirs(OBJDIR, exist_ok=True)
     compile_flags = [f for f in FLAGS if f != "-shared"]
 
     def one(src):
-        name = os.path.basename(src)
-        obj = os.path.join(objdir, name + (".part.o" if name in FORMS else ".o"))
+        obj = object_of(os.path.basename(src))
         cmd = [HIPCC] + compile_flags + ["-c", "-o", obj, src]
         if verbose:
             print(" ".join(cmd), flush=True)
@@ -54,9 +66,9 @@ def build(verbose: bool = False) -> str:
 
     with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
         objs = list(ex.map(one, sources()))
-    parts = [o for o in objs if o.endswith(".part.o")]
-    fused = os.path.join(objdir, "fused.hip.o")
-    cmd = [LLD, "-r", "-o", fused] + parts
+    parts = [object_of(s) for s in FORMS]
+    fused = os.path.join(OBJDIR, "fused.hip.o")
+    cmd = [linker(), "-r", "-o", fused] + parts
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
@@ -69,13 +81,21 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def _older(path, deps):
+    return not os.path.exists(path) or any(
+        os.path.getmtime(d) > os.path.getmtime(path) for d in deps)
+
+
 def stale() -> bool:
-    if not os.path.exists(LIB):
+    return _older(LIB, sources() + HEADERS)
+
+
+def stale_objects() -> bool:
+    """Whether an object is missing or older than what it was made from: code
+    that links the objects by hand has to build first then."""
+    if any(_older(object_of(s), [os.path.join(CSRC, s)] + HEADERS) for s in SOURCES):
         return True
-    t = os.path.getmtime(LIB)
-    deps = sources() + [os.path.join(CSRC, "tomg_internal.h"), os.path.join(CSRC, "quad.h"),
-                        os.path.join(ROOT, "include", "tomg.h")]
-    return any(os.path.getmtime(d) > t for d in deps)
+    return _older(os.path.join(OBJDIR, "fused.hip.o"), [object_of(s) for s in FORMS])
 
 
 if __name__ == "__main__":
