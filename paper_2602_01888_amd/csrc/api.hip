@@ -298,12 +298,13 @@ static hipError_t init_problem(tomg_problem *p, const tomg_config *cfg, const La
   p->bout = D(lay.bout);
   p->lc = tail_level(p, false);
   p->lcb = tail_level(p, true);
-  build_pass_args(p);
+  hipError_t e = build_pass_args(p);
+  if (e != hipSuccess) return e;
   build_tail_args(p);
   build_red_args(p);
   // queued on the stream, no host wait: a problem can be created while the
   // stream still runs other problems' work
-  hipError_t e = launch_set_slots(p, (1u << kNumSlots) - 1u, 0.0);
+  e = launch_set_slots(p, (1u << kNumSlots) - 1u, 0.0);
   if (e == hipSuccess) e = upload_args(p);
   return e;
 }

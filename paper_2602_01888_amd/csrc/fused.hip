@@ -607,26 +607,31 @@ size_t fused_max_blocks(int nx, int ny) {
 #define TOMG_PAIRS_ST 1
 #endif
 
+// Whether the band form of a pass is built: up to two sweeps with both axes
+// halved a pass has another form (pick_march takes what pick_tile leaves), and
+// the launches below are empty.  build_pass_args refuses a problem with a pass
+// that has neither.
+constexpr bool band_built(int nu, int ck) { return nu > 2 || ck != 0; }
+
 // A one-wave-block pass (stored stencils only: no such variant of the
 // level-0 pass that forms its coefficients from the tensor is built).
 template <typename T, bool EPS, int NU, int P, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
 static void launch_small(const PassArgs<T> &a, dim3 grid, hipStream_t s) {
-  if constexpr (!EPS && NU > 2)
+  if constexpr (!EPS && band_built(NU, 0))
     hipLaunchKernelGGL((k_pass<T, false, NU, P, ZERO, PROLONG, RESTRICT, NORM, 0, kBWSmall>), grid,
                        dim3(kBWSmall), 0, s, a);
 }
 
-// Both axes halved: with at most two sweeps such a pass has another form
-// (pick_march).
+// Both axes halved.
 template <typename T, bool EPS, int NU, int P, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
 static void launch_alone(const PassArgs<T> &a, dim3 grid, hipStream_t s) {
-  if constexpr (NU > 2)
+  if constexpr (band_built(NU, 0))
     hipLaunchKernelGGL((k_pass<T, EPS, NU, P, ZERO, PROLONG, RESTRICT, NORM>), grid, dim3(kBW), 0,
                        s, a);
 }
 template <typename T, bool EPS, int NU, int P, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
 static void launch_batch(int nblocks, hipStream_t s, const BatchTab &tab) {
-  if constexpr (NU > 2)
+  if constexpr (band_built(NU, 0))
     hipLaunchKernelGGL((k_pass_b<T, EPS, NU, P, ZERO, PROLONG, RESTRICT, NORM>), dim3(nblocks),
                        dim3(kBWBatch), 0, s, tab);
 }
@@ -845,8 +850,12 @@ static PassArgs<T> make_args(tomg_problem *p, int l, bool up, bool batch, T *x0,
 // Pass arguments of every level, both directions (and FP32 copies for
 // refinement problems).  The level-0 FP64 iterate is the caller's phi, set
 // per launch (nullptr here).
-void build_pass_args(tomg_problem *p) {
+hipError_t build_pass_args(tomg_problem *p) {
   ArgsBlob &g = p->hargs;
+  auto built = [&](const auto &down, const auto &up) {
+    return (down.form != kFormBand || band_built(p->cfg.nu1, down.ck)) &&
+           (up.form != kFormBand || band_built(p->cfg.nu2, up.ck));
+  };
   for (int l = 0; l + 1 < p->L; ++l)
     for (int batch = 0; batch < 2; ++batch) {
       PassArgs<double> *d64 = batch ? g.down64b : g.down64, *u64 = batch ? g.up64b : g.up64;
@@ -855,11 +864,13 @@ void build_pass_args(tomg_problem *p) {
                                  p->eyy);
       u64[l] = make_args<double>(p, l, true, batch, nullptr, p->tmp, p->f, p->exx, p->exy,
                                  p->eyy);
+      if (!built(d64[l], u64[l])) return hipErrorNotSupported;
       if (p->cfg.precision == TOMG_FP32_IR) {
         d32[l] = make_args<float>(p, l, false, batch, p->e32, p->e32b, p->r32, p->exx32,
                                   p->exy32, p->eyy32);
         u32[l] = make_args<float>(p, l, true, batch, p->e32, p->e32b, p->r32, p->exx32,
                                   p->exy32, p->eyy32);
+        if (!built(d32[l], u32[l])) return hipErrorNotSupported;
       }
     }
   if (chain_inner(p)) {
@@ -882,6 +893,7 @@ void build_pass_args(tomg_problem *p) {
     a.form = kFormBand;
     g.updown32 = a;
   }
+  return hipSuccess;
 }
 
 template <typename T>

@@ -358,7 +358,8 @@ hipError_t launch_copy_probe(const void *src, void *dst, size_t bytes, hipStream
 
 // launch arguments of every stage, built once per problem (fused.hip,
 // tail.hip, kernels.hip) and uploaded by tomg_create
-void build_pass_args(tomg_problem *p);
+// (build_pass_args: an error when a pass has no kernel in the form picked for it)
+hipError_t build_pass_args(tomg_problem *p);
 void build_tail_args(tomg_problem *p);
 void build_red_args(tomg_problem *p);
 int red_tiles(int nx, int ny);

@@ -21,7 +21,7 @@ def gpu_available():
 
 # tests that link the library's objects by hand: they get objects of the
 # present sources, not whatever an earlier build left
-LINK_OBJECTS = ("test_sanitize_cpu.py",)
+LINK_OBJECTS = ("test_sanitize_cpu.py", "test_pass_forms_cpu.py")
 
 
 def pytest_runtest_setup(item):
