@@ -784,9 +784,11 @@ static void launch_updown(int nu, const PassArgs<T> &a, hipStream_t s) {
 // there the pass moves 49 B per node for its own 4-byte iterate and a
 // chained pass saves half of them (Neumann semi-annulus at 4097^2, four
 // inner cycles per step: 18.7 -> 17.2 ms).  With the coefficients formed
-// from the tensor the level-0 pass is bound by its steps' phase chain, not
-// by its bytes, and the chained pass's sixteen colour phases per step made
-// it slower than the two passes it replaces (295 against 135 + 134 us).
+// from the tensor the level-0 pass on bands in LDS was bound by its steps'
+// phase chain, not by its bytes, and the chained pass's sixteen colour phases
+// per step made it slower than the two passes it replaced (295 against 135 +
+// 134 us); the marching passes that do this work now (108 + 115 us) have not
+// been chained.
 // Nor where level 0 is on tiles (semi-annulus, FP32: 1025^2 64 us chained
 // against 22 + 23, 513^2 46 against 8 + 10).
 bool chain_inner(const tomg_problem *p) {
@@ -1007,9 +1009,9 @@ template int fused_up<float>(tomg_problem *, int, const float *, float *, const 
 // ---------------------------------------------------------------------------
 
 // Nodes of a level over the whole batch up to which its passes run as alone.
-// A burst of 24 problems of sides 129 .. 2049 (mixed precision): 15.45 ms with
-// 0, 14.37 with 1.2 M, 13.91 with this, 13.88 with 5 M; 256 resident problems
-// of sides 65 .. 1025: 23.5, 23.4, 23.3, 23.3 ms.
+// A burst of 24 problems of sides 129 .. 2049 (mixed precision): 12.8 ms with 0,
+// 12.4 with 1.2 M, 12.3 with this and with 5 M; 256 resident problems of sides
+// 65 .. 1025: 19.8, 19.8, 19.7, 19.9 ms.
 constexpr long kFewNodes = 2500000;
 template <typename T>
 static void batch_pass(tomg_problem *const *probs, const int *idx, int cnt, int l, bool up,

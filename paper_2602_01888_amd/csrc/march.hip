@@ -7,13 +7,15 @@
 // lane idles in a colour phase.  The rows in flight -- node values and
 // coefficients -- stay in registers, in rings indexed by compile-time slots,
 // and a neighbour's value in the next lane comes by a one-lane wave shift
-// (DPP), so a block is one wave with no LDS and no barrier.  The passes that
-// kept node values in LDS, one column per thread, spent a step's time in
-// eleven barrier phases with half the lanes idle.  A pass of 4097^2, those ->
-// this form: FP64 239 -> 181 us (856 MB, 3.6 -> 4.7 TB/s), FP32 129 -> 105 us
-// (3.4 -> 4.1 TB/s); of a batch of 256 problems of sides 65 .. 1025, FP64 39.1
-// -> 34.1 ms, mixed precision 26.7 -> 23.9 ms.  What is left is the walk
-// itself: a copy of the same bands streams 4.3 .. 4.7 TB/s.
+// (DPP), so a block is one wave without a barrier, and LDS holds only what a
+// lane keeps for itself.  The passes that kept node values in LDS, one column
+// per thread, spent a step's time in eleven barrier phases with half the lanes
+// idle.  A pass of 4097^2, those -> this form: FP64 264 -> 200 us upward with
+// its norm, 235 -> 195 us downward (856 MB, 4.3 and 4.4 TB/s); FP32 129 -> 115
+// and 128 -> 108 us (436 MB, 3.8 and 4.0 TB/s); a batch of 256 problems of sides
+// 65 .. 1025, FP64 39.1 -> 34.1 ms, mixed precision 26.7 -> 23.9 ms.  What is
+// left is the walk itself: without its arithmetic it takes 180 us in FP64 and
+// 107 us in FP32.
 // With the stencil stored (nine planes: 2049^2 FP64 is 437 MB a pass) the same:
 // the upward pass with its norm 115 -> 96 us, the downward pass 102 -> 97 us
 // (4.5 TB/s), 256 problems of mixed precision 21.1 -> 20.3 ms.  Its six rows of
@@ -435,7 +437,7 @@ done:
 // takes 256 VGPRs and 20 .. 30 of the accumulation file, FP32 140 .. 150; held
 // to two waves FP64 spills to scratch (a 4097^2 cycle 825 against 752 us), as
 // does FP32 at four (two cycles and their refinement step 1408 against 1131
-// us).  The stored rows take 512 and 256 registers: one wave and two.
+// us).  With a stored stencil it is up to 446 and 219 registers: one wave and two.
 template <typename T, bool ST>
 constexpr int march_waves() {
   return sizeof(T) == 8 ? 1 : (ST ? 2 : 3);
@@ -478,8 +480,10 @@ void launch_nu(int nu, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab,
 
 }  // namespace
 
-// Gives a pass the marching form: both axes halved, at most two sweeps (three
-// sweeps' rows do not fit the registers).
+// Gives a pass the marching form: both axes halved, at most two sweeps.  (From
+// the tensor a sweep more takes some 95 registers in FP64 and 50 in FP32, with a
+// stored stencil 120 .. 145 and 55: by that count only stored FP64 passes of
+// three and four would not fit a wave's 512.  None are built or measured.)
 template <typename T>
 bool pick_march(PassArgs<T> &a, int nu, bool batch) {
   if (nu > 2 || a.ck != 0) return false;

@@ -283,20 +283,35 @@ void launch_ck(int nu, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab,
 
 }  // namespace
 
-// Gives the pass the tile form where it is the faster one: alone, at most two
-// sweeps (the halo of four is wider than the tile).
-// Measured per pass (down, up; V(2,2), FP64, a cycle of 4097^2), marching
-// -> tiles: 65^2 13.1, 14.1 -> 5.8, 5.3 us; 129^2 12.9, 12.4 -> 6.2, 5.8;
-// 257^2 14.7, 16.4 -> 7.9, 6.2; 513^2 21.7, 22.0 -> 15.7, 12.6; 1025^2 39.1,
-// 38.7 -> 36.4, 36.4.  At 2049^2 the two are even (a cycle of a 2049^2
-// problem 295 -> 305 us, FP32 470 -> 464), and the level-0 passes of 4097^2
-// are slower (310 against 240 us a pass).  Small grids take the 32 x 32 tiles,
-// for more blocks; from 257^2 up there are enough of the larger ones, which
-// recompute less halo (a 513^2 cycle 71.5 us with them, 77.7 without).
+// Gives the pass the tile form: alone, at most two sweeps (the halo of four is
+// wider than the tile), levels up to 1.2 M nodes, where the bands in LDS, then
+// the other form of these levels, took over: 65^2 13.1, 14.1 -> 5.8, 5.3 us a
+// pass (down, up; FP64), 129^2 12.9, 12.4 -> 6.2, 5.8, 257^2 14.7, 16.4 -> 7.9,
+// 6.2, 513^2 21.7, 22.0 -> 15.7, 12.6, 1025^2 39.1, 38.7 -> 36.4, 36.4.
+// Against the marching form, us a pass, marching / tiles, V(2,2):
+//               FP64, tensor            FP64, stored            FP32, tensor
+//               down       up           down       up           down       up
+//   257^2       10.6/6.6   9.7/6.3      13.0/6.9   11.5/6.6     8.9/6.1    8.4/5.6
+//   513^2       12.8/9.9   11.6/11.7    16.0/14.4  14.3/14.9    12.2/8.3   10.2/6.3
+//   769^2       15.1/14.6  14.7/14.8    23.4/21.3  21.3/21.4    15.0/10.7  13.5/10.7
+//   1025^2      20.4/22.1  20.0/21.0    31.1/36.5  27.5/35.4    16.8/15.6  15.0/14.2
+//   1217x1025   23.0/25.1  22.3/24.8    33.6/42.8  30.7/43.4    17.3/17.2  15.7/15.9
+//   1537^2      31.5/43.0  31.2/42.8    51.6/79.3  46.5/81.0    23.2/27.9  22.8/23.8
+//   2049^2      50.8/71.7  51.3/72.9    97.0/139   93.9/139     29.7/46.1  27.3/42.4
+// (coarse levels, stored, from zero: 1025^2 FP64 29.4/34.4, 27.6/34.7, FP32
+// 19.7/21.5, 20.8/21.3; 769^2 21.2/20.2, 21.4/20.0 and 14.8/13.1, 14.1/14.1).
+// So 1.2 M is where FP32 passes from the tensor change over; FP64 passes do at
+// 0.6 M nodes, and those of a million lose 5 .. 30 % here.  Small grids take
+// the 32 x 32 tiles, for more blocks; from 257^2 up there are enough of the
+// larger ones, which recompute less halo (a 513^2 cycle 71.5 us with them, 77.7
+// without).
 // In a batch that fills the device the marching passes, which recompute less
-// still, are the faster from 257^2 up (256 problems of sides 65 .. 1025, mixed
-// precision: no tiles 23.87 ms, up to 65^2 23.63, 129^2 23.50, 257^2 24.98,
-// 513^2 26.34; FP64 34.10, 33.45, 32.52, 34.00, 34.90).
+// halo, are the faster from 257^2 up and even below.  256 problems of sides 65
+// .. 1025, mixed precision and FP64, tiles on no level 19.5 and 25.4 ms, up to
+// 65^2 19.55 and 25.8, 129^2 19.7 and 25.9, 257^2 20.2 and 26.6, 513^2 21.8 and
+// 28.8; a burst of 24 requests 12.1, 12.1, 12.3, 12.6 and 12.7 ms.  (Before its
+// arguments lay in scalar registers and the stored passes marched, a batch was
+// fastest with tiles up to 129^2.)
 // One axis halved (semi-annulus of 1537 x 769, stored, FP32; bands -> tiles):
 // level 1, 769 x 769, 23, 22 -> 14, 14 us; level 0, whose bands ran chained
 // in 66 us with the next cycle's downward pass, 23 + 27.
