@@ -12,9 +12,9 @@
 // holds the launches of all and the band form, which takes any sweep count
 // and grid transfer.  Up to two sweeps the others are faster and have most of
 // the work: whole tiles on small and middle levels (tile.hip), one wave
-// marching on large ones (march.hip).  The bands keep three and four sweeps,
-// semi-coarsened transfers of large levels and of batches, and the chained
-// pass of the FP32 inner cycles.
+// marching on large ones (march.hip).  The bands keep three and four sweeps
+// (but for the small levels of FP64 batches, on tiles), semi-coarsened transfers
+// of large levels and of batches, and the chained pass of the FP32 inner cycles.
 //
 // Block geometry of the band form: BW threads own BW consecutive columns (one
 // each); the H = 4 nu + 2 outer columns on either side are halo, recomputed
@@ -837,7 +837,7 @@ static PassArgs<T> make_args(tomg_problem *p, int l, bool up, bool batch, T *x0,
                      (long)a.nx * a.ny <= kSmallPassNodes;
   a.ck = v.ck;
   // the residual follows the sweeps in a down pass and where the norm is taken
-  if (pick_tile(a, nu, !up || (l == 0 && !f32), batch)) return a;
+  if (pick_tile(a, l, nu, !up || (l == 0 && !f32), batch)) return a;
   if (pick_march(a, nu, batch)) return a;
   a.bw = batch ? kBWBatch : (small ? kBWSmall : kBW);
   a.W = a.bw - 2 * (4 * nu + 2);

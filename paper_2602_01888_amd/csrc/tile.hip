@@ -271,8 +271,19 @@ void launch_nu(int nu, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab,
   else
     launch_shape<T, EPS, 2, ZERO, PROLONG, RESTRICT, NORM, 16, 16, CK>(a, s, tab, nb);
 }
+// Three and four sweeps: FP64 levels below the first in a batch (pick_tile).
+template <typename T, bool EPS, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
+constexpr bool many_sweeps() {
+  return std::is_same<T, double>::value && !EPS && !NORM && (ZERO || PROLONG);
+}
 template <typename T, bool EPS, bool ZERO, bool PROLONG, bool RESTRICT, bool NORM>
 void launch_ck(int nu, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab, int nb) {
+  if constexpr (many_sweeps<T, EPS, ZERO, PROLONG, RESTRICT, NORM>()) {
+    if (nu == 3)
+      return launch_shape<T, EPS, 3, ZERO, PROLONG, RESTRICT, NORM, 32, 16, 0>(a, s, tab, nb);
+    if (nu == 4)
+      return launch_shape<T, EPS, 4, ZERO, PROLONG, RESTRICT, NORM, 32, 16, 0>(a, s, tab, nb);
+  }
   if (a.ck == 0)
     launch_nu<T, EPS, ZERO, PROLONG, RESTRICT, NORM, 0>(nu, a, s, tab, nb);
   else if (a.ck == 1)
@@ -283,11 +294,11 @@ void launch_ck(int nu, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab,
 
 }  // namespace
 
-// Gives the pass the tile form: alone, at most two sweeps (the halo of four is
-// wider than the tile), levels up to 1.2 M nodes, where the bands in LDS, then
-// the other form of these levels, took over: 65^2 13.1, 14.1 -> 5.8, 5.3 us a
-// pass (down, up; FP64), 129^2 12.9, 12.4 -> 6.2, 5.8, 257^2 14.7, 16.4 -> 7.9,
-// 6.2, 513^2 21.7, 22.0 -> 15.7, 12.6, 1025^2 39.1, 38.7 -> 36.4, 36.4.
+// Gives the pass the tile form: up to two sweeps (of three or four the halo is
+// wider than the tile), alone on levels up to 1.2 M nodes, where the bands in
+// LDS, then the other form of these levels, took over: 65^2 13.1, 14.1 -> 5.8,
+// 5.3 us a pass (down, up; FP64), 129^2 12.9, 12.4 -> 6.2, 5.8, 257^2 14.7, 16.4
+// -> 7.9, 6.2, 513^2 21.7, 22.0 -> 15.7, 12.6, 1025^2 39.1, 38.7 -> 36.4, 36.4.
 // Against the marching form, us a pass, marching / tiles, V(2,2):
 //               FP64, tensor            FP64, stored            FP32, tensor
 //               down       up           down       up           down       up
@@ -312,17 +323,28 @@ void launch_ck(int nu, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab,
 // 28.8; a burst of 24 requests 12.1, 12.1, 12.3, 12.6 and 12.7 ms.  (Before its
 // arguments lay in scalar registers and the stored passes marched, a batch was
 // fastest with tiles up to 129^2.)
+// Three and four sweeps, FP64, in a batch: levels below the first up to 65^2.
+// An FP32 batch has them in the tail, whose FP64 form starts at 33^2, and a
+// band of 65^2 is a long chain on few blocks: 16 problems of 257^2, V(3,3), 2070
+// us on bands, 1715 on tiles; 200 of 129^2 5300 and 4320.
 // One axis halved (semi-annulus of 1537 x 769, stored, FP32; bands -> tiles):
 // level 1, 769 x 769, 23, 22 -> 14, 14 us; level 0, whose bands ran chained
 // in 66 us with the next cycle's downward pass, 23 + 27.
 constexpr long kTileNodes = 1200000;      // largest level on tiles
 constexpr long kSmallTileNodes = 20000;   // largest level on 32 x 32 tiles
 constexpr long kTileNodesBatch = 20000;   // largest level on tiles in a batch
+constexpr long kManySweepNodes = 65 * 65;  // largest level on tiles with three or four sweeps
 template <typename T>
-bool pick_tile(PassArgs<T> &a, int nu, bool res, bool batch) {
+bool pick_tile(PassArgs<T> &a, int l, int nu, bool res, bool batch) {
   const long n = (long)a.nx * a.ny;
-  if (nu > 2 || n > (batch ? kTileNodesBatch : kTileNodes)) return false;
-  a.form = n > kSmallTileNodes ? kFormTileLarge : kFormTileSmall;
+  if (nu > 2) {
+    if (!std::is_same<T, double>::value || !batch || l == 0 || a.ck != 0 || n > kManySweepNodes)
+      return false;
+    a.form = kFormTileLarge;
+  } else {
+    if (n > (batch ? kTileNodesBatch : kTileNodes)) return false;
+    a.form = n > kSmallTileNodes ? kFormTileLarge : kFormTileSmall;
+  }
   const int hx = 8 * nu + (res ? 2 : 0), hy = 4 * nu + (res ? 2 : 0);
   a.W = (a.form == kFormTileLarge ? 64 : 32) - hx;
   a.CH = 32 - hy;
@@ -331,8 +353,8 @@ bool pick_tile(PassArgs<T> &a, int nu, bool res, bool batch) {
   a.xcd_order = 0;
   return true;
 }
-template bool pick_tile<double>(PassArgs<double> &, int, bool, bool);
-template bool pick_tile<float>(PassArgs<float> &, int, bool, bool);
+template bool pick_tile<double>(PassArgs<double> &, int, int, bool, bool);
+template bool pick_tile<float>(PassArgs<float> &, int, int, bool, bool);
 
 template <typename T>
 void tile_down(int nu, bool eps, bool zero, const PassArgs<T> &a, hipStream_t s, const BatchTab *tab, int nb) {

@@ -310,7 +310,7 @@ void fused_updown(tomg_problem *p, const T *pong, T *out, const T *b, const T *e
 // and blocking where they are the faster (res: the pass forms residuals),
 // the others launch it (tab, nb: a batched launch and its blocks).
 template <typename T>
-bool pick_tile(PassArgs<T> &a, int nu, bool res, bool batch);
+bool pick_tile(PassArgs<T> &a, int l, int nu, bool res, bool batch);
 template <typename T>
 void tile_down(int nu, bool eps, bool zero, const PassArgs<T> &a, hipStream_t s,
                const BatchTab *tab, int nb);
